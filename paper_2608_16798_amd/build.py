@@ -2,8 +2,7 @@
 
 Usage: python -m paper_2608_16798_amd.build   (or call build()).
 Every call recompiles; objects go to paper_2608_16798_amd/_build/.
-RLK_EXTRA_FLAGS (environment) appends hipcc flags, e.g. "-DRLK_KS=64 -DRLK_NSTAGE=4" for the GEMM
-pipeline geometry.
+RLK_EXTRA_FLAGS (environment) appends hipcc flags.
 
 Host sanitizers: python -m paper_2608_16798_amd.build --host-sanitizers builds librlk_hostsan.so,
 whose host code (argument validation, workspace layout, the chunk plan, the prefix-tree packer)

@@ -7,97 +7,69 @@
 // In the token-reference layout (dz = diag(s) q) the gradient GEMMs read the forward's q and q^T
 // as A, the dhidden epilogue scales its rows by s and the dW GEMM's B is (diag(s) hidden)^T.
 //
-// Tile geometry (gfx950): a 256 x 256 output tile per workgroup of WAVES_M x WAVES_N = 2 x 4
-// wavefronts (two per SIMD), each owning a 128 x 64 block of 32 x 32 v_mfma_f32_32x32x16_bf16
-// tiles (fp32 operands use v_mfma_f32_32x32x2_f32) with its 128 fp32 accumulators per lane in
-// the unified register file.  Operands stream through LDS in K slices of KS bytes per row,
-// copied straight from global memory by buffer_load ... lds (no staging registers) into NSTAGE
-// buffers; rows are XOR-swizzled at 16-byte granularity so MFMA fragment reads are bank-conflict
-// free.  Each lane's MFMA fragment carries 8
-// consecutive K elements of one row (16 bytes); A and B use the same K assignment, so the lane
+// Tile geometry (gfx950): a 256 x 256 output tile per workgroup of 2 x 4 wavefronts, two per SIMD.
+// The tile is four 128 x 128 quadrants; in each, wavefront (wm, wn) owns the 64 x 32 block at
+// (64 wm, 32 wn), as 4 x 2 blocks of 16 x 16 (v_mfma_f32_16x16x32_bf16; fp32 operands use
+// v_mfma_f32_16x16x4_f32), so its 128 fp32 accumulators cover every half of either operand.  Operands
+// stream through LDS in K slices of 128 bytes per row, copied straight from global memory by
+// buffer_load ... lds (no staging registers) into two buffers of half tiles (128 rows); rows are
+// XOR-swizzled at 16-byte granularity so the fragment reads are bank-conflict free.  Each lane's MFMA
+// fragment carries 16 consecutive bytes of one row; A and B use the same K assignment, so the lane
 // split of K inside the MFMA is irrelevant to the sum.
 //
 // The gradient GEMMs of shapes with few output tiles split K over several workgroups per tile
 // (fp32 partials in the workspace, summed in split order by k_splitk_reduce).
 //
-// Output layout of a 32x32 MFMA block: lane l holds column (l % 32); accumulator register r
-// holds row 8*(r/4) + 4*(l/32) + (r%4).  With vocabulary on M and tokens on N, every lane's
-// accumulators belong to a single token, so the vocabulary reduction of the online
-// log-softmax is in-register, then one cross-half exchange, then one LDS exchange between
-// the wavefronts of a column.
+// Output layout of a 16x16 MFMA block D = X Y^T: lane l holds column l % 16 (a row of Y), register r
+// row 4 (l / 16) + r (a row of X).  The forward takes X = vocabulary and Y = tokens, so every lane's
+// accumulators belong to one token per column block and the vocabulary reduction of the online
+// log-softmax is in-register, then over the four lane groups, then one LDS exchange between the two
+// wavefronts of a column.  The gradient GEMMs take X = features, so a lane's four registers are
+// consecutive in the row-major output and leave in one store.
 #include "rlk_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace rlk {
 
 namespace {
 
-#ifndef RLK_KS
-#define RLK_KS 128
-#endif
-#ifndef RLK_NSTAGE
-#define RLK_NSTAGE 2
-#endif
-#ifndef RLK_WAVES_N
-#define RLK_WAVES_N 4
-#endif
-constexpr int WAVES_M = 2;
-constexpr int WAVES_N = RLK_WAVES_N;    // 2: one wavefront per SIMD; 4: two per SIMD
+constexpr int WAVES_M = 2, WAVES_N = 4;
 constexpr int NWAVE = WAVES_M * WAVES_N;
 constexpr int NT = 64 * NWAVE;
-constexpr int WTM = kTile / WAVES_M;    // rows of a wavefront's block
-constexpr int WTN = kTile / WAVES_N;    // columns of a wavefront's block
-constexpr int MBW = WTM / 32;           // 32x32 MFMA tiles per wavefront along M
-constexpr int NBW = WTN / 32;           // ... along N
-constexpr int KS = RLK_KS;              // bytes of K per pipeline slice per row (kGemmSliceBytes)
-constexpr int NSTAGE = RLK_NSTAGE;      // LDS buffers in the copy pipeline
+constexpr int HALF = kTile / 2;         // rows of a half tile
+constexpr int WTM = HALF / WAVES_M;     // rows of a wavefront's block in a quadrant
+constexpr int WTN = HALF / WAVES_N;     // columns of it
+constexpr int MB = WTM / 16, NB = WTN / 16;  // 16x16 MFMA blocks of it
+constexpr int KS = kGemmSliceBytes;     // bytes of K per pipeline slice per row
 constexpr int CPR = KS / 16;            // 16-byte chunks per row of a slice
 constexpr int RPI = 64 / CPR;           // rows per LDS-DMA instruction
-constexpr int IPW = kTile / RPI / NWAVE;  // LDS-DMA instructions per wavefront per operand
-constexpr int NKK = KS / 32;            // MFMA K steps per slice
-constexpr int DMA_PER_SLICE = 2 * IPW;  // vector-memory instructions per wavefront per slice
-constexpr int OPND_B = kTile * KS;      // one operand's slice
-constexpr int STAGE_B = 2 * OPND_B;     // A + B
-constexpr int PIPE_B = NSTAGE * STAGE_B;
-static_assert(PIPE_B <= 131072 && KS == kGemmSliceBytes && IPW >= 1, "pipeline geometry");
+constexpr int IPH = HALF / RPI / NWAVE; // LDS-DMA instructions per wavefront per half tile
+constexpr int HALF_B = HALF * KS;       // a half tile in LDS
+constexpr int OPND_B = 4 * HALF_B;      // one operand: two buffers of two half tiles
+constexpr int PIPE_B = 2 * OPND_B;      // A then B
+static_assert(KS == 128 && IPH == 2 && WTM == 64 && WTN == 32, "pipeline geometry");
 constexpr int QROW = kTile * 2 + 16;    // LDS row stride of the bf16 probability tile (bytes)
 constexpr int RED_OFF = kTile * QROW;   // 135168: reduction scratch after the staged tile
 // The staged tile holds token t's 16-byte vocabulary chunk c at chunk c ^ qswz(t) of row t, so that
 // the transposing reads of 8 tokens 8 apart (same chunk) fall in distinct bank groups.
 __device__ __forceinline__ int qswz(int t) { return (t >> 3) & 7; }
-constexpr int LDS_B = RED_OFF + 3 * WAVES_M * kTile * 4;  // >= PIPE_B
+constexpr int LDS_B = RED_OFF + 3 * WAVES_M * kTile * 4;
+static_assert(LDS_B >= PIPE_B && LDS_B <= 163840, "LDS of a compute unit");
 constexpr int GROUP_M = 16;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kBufferFlags = 0x00020000;  // raw buffer: 32-bit data format, offset range-checked
 
 #define LDSP(p) ((__attribute__((address_space(3))) void*)(p))
 
-// Scheduling hints for one MFMA K step: interleave the LDS fragment reads (and the global->LDS
-// copies of the next slice) with the MFMA chain.
-template <int NMFMA, int NDS, int NVMEM>
-__device__ __forceinline__ void sched_step() {
-#pragma unroll
-  for (int i = 0; i < NMFMA; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-    if constexpr (NVMEM > 0) {
-      if (i * NVMEM / NMFMA != (i + 1) * NVMEM / NMFMA) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-      if ((i + 1) * NVMEM / NMFMA - i * NVMEM / NMFMA > 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    }
-    if (i < NDS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
-  }
-}
-
-// 16-byte-chunk XOR swizzle of an LDS row (CPR chunks).  A 16-byte fragment read serves 16 lanes
-// = 16 consecutive rows per cycle; with 128-byte rows two rows share one 256-byte bank window, and
+// 16-byte-chunk XOR swizzle of an LDS row of 8 chunks.  A 16-byte fragment read serves 16 lanes =
+// 16 consecutive rows per cycle; with 128-byte rows two rows share one 256-byte bank window, and
 // (row parity, chunk ^ swz(row)) is distinct over the 16 rows, so the reads are conflict free.
-// swz depends on r mod 16 only: the fragment addresses of a wavefront's 32-row MFMA blocks then
-// differ by immediate offsets, and a copy's lane offset depends on its instruction only through
-// the instruction's parity.
-__device__ __forceinline__ int swz(int r) {
-  if constexpr (CPR == 8) return (r >> 1) & 7;
-  else return (r >> 1) & 3;
-}
+// swz depends on r mod 16 only: the fragment addresses of a wavefront's 16-row blocks then differ by
+// immediate offsets, and a copy's lane offset depends on its instruction only through the
+// instruction's parity.
+__device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding: vmcnt[3:0] in
 // bits 3:0, vmcnt[5:4] in bits 15:14, expcnt 7 and lgkmcnt 15 = no wait).
@@ -106,25 +78,17 @@ __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
-__device__ __forceinline__ void wait_vmcnt_dyn(int n) {
-  if (n >= 48) wait_vmcnt<48>();
-  else if (n >= 32) wait_vmcnt<32>();
-  else if (n >= 24) wait_vmcnt<24>();
-  else if (n >= 16) wait_vmcnt<16>();
-  else if (n >= 8) wait_vmcnt<8>();
-  else if (n >= 4) wait_vmcnt<4>();
-  else wait_vmcnt<0>();
-}
 // LDS/scalar counter to zero, vector memory unconstrained.
 __device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 
 // Workgroup barrier without a memory fence: the copies still in flight must stay in flight, so
-// the waits are explicit (above); the empty asm statements keep the compiler from moving memory
-// accesses across the barrier.
+// the waits are explicit (above); nothing is scheduled across it.
 __device__ __forceinline__ void block_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 enum { EPI_FWD = 0, EPI_DH = 1, EPI_DW = 2 };
@@ -134,19 +98,19 @@ struct Op;
 
 template <>
 struct Op<bf16_t> {
-  static __device__ __forceinline__ void mma(f32x16& c, u32x4 a, u32x4 b) {
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+  static __device__ __forceinline__ void mma(f32x4& c, u32x4 x, u32x4 y) {
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c,
                                                 0, 0, 0);
   }
 };
 
 template <>
 struct Op<float> {
-  static __device__ __forceinline__ void mma(f32x16& c, u32x4 a, u32x4 b) {
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+  static __device__ __forceinline__ void mma(f32x4& c, u32x4 x, u32x4 y) {
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x.x), __uint_as_float(y.x), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x.y), __uint_as_float(y.y), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x.z), __uint_as_float(y.z), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x.w), __uint_as_float(y.w), c, 0, 0, 0);
   }
 };
 
@@ -161,12 +125,13 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-template <typename T>
-__device__ __forceinline__ void store_elem(T* p, float x);
-template <>
-__device__ __forceinline__ void store_elem<float>(float* p, float x) { *p = x; }
-template <>
-__device__ __forceinline__ void store_elem<bf16_t>(bf16_t* p, float x) { p->bits = bf16_bits(x); }
+// four consecutive output elements (16-byte aligned fp32, 8-byte aligned bf16)
+__device__ __forceinline__ void store4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
+__device__ __forceinline__ void store4(bf16_t* p, f32x4 v) {
+  *reinterpret_cast<u32x2*>(p) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+}
+__device__ __forceinline__ void store_elem(float* p, float x) { *p = x; }
+__device__ __forceinline__ void store_elem(bf16_t* p, float x) { p->bits = bf16_bits(x); }
 
 // XCD-aware tile mapping.  Workgroup ids are dispatched round-robin over the 8 XCDs, so the 256
 // workgroups resident at a time are 256 consecutive ids.  Tiles are rastered in column groups of
@@ -195,14 +160,6 @@ __device__ __forceinline__ bool map_tile(int tm, int tn, int& tile_m, int& tile_
   return true;
 }
 
-// DEEP_B: the B operand streams through three LDS stages (A through two; 5 x 32 KiB = all 160 KiB),
-// so B is copied two slices ahead instead of one.  The main loop waits on copy latency (copies issued
-// later in a slice measured 2-8 % slower), and the forward GEMM, whose tiles are short (K = d), runs
-// 2.0-2.3 % faster this way; the dhidden and dW GEMMs ran 3-4 % and 0.5 % slower, so they keep two
-// stages of each operand.
-constexpr int LDS_DEEP_B = 5 * OPND_B;
-static_assert(LDS_DEEP_B <= 163840 && LDS_DEEP_B >= LDS_B, "three-stage pipeline fits the LDS");
-
 // Reference of the stored probabilities of chunk column n in a forward tile with maximum m: m itself,
 // or with a.zr (token-reference layout) the column's reference logit r, clamped to m - kRefSpan where
 // it lies further below (then, with mark, the chunk is flagged: its dz needs the explicit pass).
@@ -217,8 +174,7 @@ __device__ __forceinline__ float tile_ref(const GemmArgs& a, float m, int n, int
 
 template <typename T, int EPI, bool STORE_Q, bool KTAIL>
 __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
-  constexpr bool DEEP_B = EPI == EPI_FWD && sizeof(T) == 2;
-  __shared__ __attribute__((aligned(16))) char smem[DEEP_B ? LDS_DEEP_B : LDS_B];
+  __shared__ __attribute__((aligned(16))) char smem[EPI == EPI_FWD ? LDS_B : PIPE_B];
 
   int M = a.M, N = a.N, K = a.K;
   // rows of the chunk: every trained token for the forward, those with a surrogate gradient for the
@@ -238,18 +194,15 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wid / WAVES_N, wn = wid % WAVES_N;
-  const int lrow = lane & 31, lh = lane >> 5;
+  const int lr = lane & 15, lg = lane >> 4;
 
   // ---- operand panels as buffer resources: rows beyond M/N (and, with KTAIL, K chunks beyond K)
   // read as zero through the hardware range check; 32-bit offsets address one 256-row panel.
   const uint32_t lda_b = (uint32_t)(a.lda * (int64_t)sizeof(T)), ldb_b = (uint32_t)(a.ldb * (int64_t)sizeof(T));
   const int rows_a = min(kTile, M - tile_m * kTile), rows_b = min(kTile, N - tile_n * kTile);
-  const __amdgpu_buffer_rsrc_t rsa = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(reinterpret_cast<const char*>(a.A) + (int64_t)tile_m * kTile * lda_b), (short)0,
-      (int)((uint32_t)rows_a * lda_b), kBufferFlags);
-  const __amdgpu_buffer_rsrc_t rsb = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(reinterpret_cast<const char*>(a.B) + (int64_t)tile_n * kTile * ldb_b), (short)0,
-      (int)((uint32_t)rows_b * ldb_b), kBufferFlags);
+  char* const pa = const_cast<char*>(reinterpret_cast<const char*>(a.A) + (int64_t)tile_m * kTile * lda_b);
+  char* const pb = const_cast<char*>(reinterpret_cast<const char*>(a.B) + (int64_t)tile_n * kTile * ldb_b);
+  const uint32_t size_a = (uint32_t)rows_a * lda_b, size_b = (uint32_t)rows_b * ldb_b;
   const int64_t Kb = (int64_t)K * sizeof(T);
   int nk = (int)((Kb + KS - 1) / KS);
   // split K: this workgroup covers slices [ks0, ks0 + nk) of the tile's K range
@@ -261,225 +214,238 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
 
   // Direct global->LDS copies (LDS DMA): one instruction moves 64 lanes x 16 bytes into 1 KiB of
   // LDS at consecutive addresses, i.e. RPI rows of one K slice.  Wave w fills rows
-  // [w * IPW * RPI, (w + 1) * IPW * RPI) of each operand with IPW instructions; lane l of
-  // instruction j carries row (w * IPW + j) * RPI + l / CPR into LDS slot l % CPR, which holds the
-  // logical 16-byte K chunk (l % CPR) ^ swz(row).
-  // The lane part of a copy's offset depends on the instruction only through its parity; the row
-  // part is uniform and goes into the scalar offset.
-  static_assert(RPI % 2 == 0 || RPI == 1, "copy geometry");
-  uint32_t voa[2], vob[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int row = (wid * IPW + j) * RPI + lane / CPR;
-    const int chunk = (lane % CPR) ^ swz(row);
-    voa[j] = (uint32_t)(lane / CPR) * lda_b + chunk * 16;
-    vob[j] = (uint32_t)(lane / CPR) * ldb_b + chunk * 16;
-  }
+  // [w * IPH * RPI, (w + 1) * IPH * RPI) of each half tile; lane l of instruction j carries row
+  // (w * IPH + j) * RPI + l / CPR into LDS slot l % CPR, which holds the logical 16-byte K chunk
+  // (l % CPR) ^ swz(row).  The row part of the address is uniform and goes into the scalar offset.
   // Rows past the panel (ragged last tiles) read as zero because their vector offset alone is out of
   // range: 0x80000000 >= num_records (every 256-row panel is at most 2 GiB, checked by the host), so
   // the read stays inside the panel whether or not the hardware adds the scalar offset to the check.
-  // A lane's row is r0 + lane / CPR; it is past the panel when r0 >= rows - lane / CPR.
-  const int lim_a = rows_a - lane / CPR, lim_b = rows_b - lane / CPR;
-  // copies of slice kt for the rows owned by wavefront w
-  auto dma_w = [&](int kt, int w) {
-    char* st = smem + (kt % NSTAGE) * STAGE_B;
-    const uint32_t kb = (uint32_t)(kt + ks0) * KS;
+  uint32_t vo_a[2][IPH], vo_b[2][IPH];
 #pragma unroll
-    for (int j = 0; j < IPW; ++j) {
-      const uint32_t r0 = (uint32_t)((w * IPW + j) * RPI);
-      uint32_t oa = (int)r0 < lim_a ? voa[j & 1] : 0x80000000u;
-      uint32_t ob = (int)r0 < lim_b ? vob[j & 1] : 0x80000000u;
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int j = 0; j < IPH; ++j) {
+      const int row = (wid * IPH + j) * RPI + lane / CPR;
+      const int chunk = (lane % CPR) ^ swz(row);
+      vo_a[h][j] = h * HALF + row < rows_a ? (uint32_t)(lane / CPR) * lda_b + chunk * 16 : 0x80000000u;
+      vo_b[h][j] = h * HALF + row < rows_b ? (uint32_t)(lane / CPR) * ldb_b + chunk * 16 : 0x80000000u;
+    }
+  // this wavefront's copies of half h of one operand of slice kt into buffer kt % 2.  Slices past the
+  // last one are copied from an empty panel (zeros, no memory access), which keeps the number of
+  // copies in flight the same to the end of the loop.
+  auto copy_half = [&](bool op_b, int h, int kt, int buf) {
+    const uint32_t kb = (uint32_t)(kt + ks0) * KS;
+    const uint32_t size = kt < nk ? (op_b ? size_b : size_a) : 0u;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(op_b ? pb : pa, (short)0, (int)size, kBufferFlags);
+#pragma unroll
+    for (int j = 0; j < IPH; ++j) {
+      uint32_t o = op_b ? vo_b[h][j] : vo_a[h][j];
       if constexpr (KTAIL) {
         // chunks past the end of K would read the next row: push them out of range (zero fill)
-        const int row = (w * IPW + j) * RPI + lane / CPR;
-        const uint32_t ck = kb + (((lane % CPR) ^ swz(row)) * 16);
-        if ((int64_t)ck >= Kb) {
-          oa = 0x80000000u;
-          ob = 0x80000000u;
-        }
-      }
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsa, LDSP(st + (w * IPW + j) * 1024), 16, oa, kb + r0 * lda_b, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsb, LDSP(st + OPND_B + (w * IPW + j) * 1024), 16, ob,
-                                               kb + r0 * ldb_b, 0, 0);
-    }
-  };
-  auto dma = [&](int kt) { dma_w(kt, wid); };
-  // LDS offsets of slice kt's operand panels: two stages of A + B (STAGE_B each), or with DEEP_B
-  // three B buffers at 0, 32, 64 KiB and two A buffers at 96, 128 KiB.
-  auto off_a = [&](int kt) { return DEEP_B ? 3 * OPND_B + (kt % 2) * OPND_B : (kt % NSTAGE) * STAGE_B; };
-  auto off_b = [&](int kt) { return DEEP_B ? (kt % 3) * OPND_B : (kt % NSTAGE) * STAGE_B + OPND_B; };
-  // copies of one operand of slice kt (DEEP_B pipeline)
-  auto dma_op = [&](bool op_a, int kt) {
-    const uint32_t kb = (uint32_t)(kt + ks0) * KS;
-#pragma unroll
-    for (int j = 0; j < IPW; ++j) {
-      const uint32_t r0 = (uint32_t)((wid * IPW + j) * RPI);
-      uint32_t o = op_a ? ((int)r0 < lim_a ? voa[j & 1] : 0x80000000u) : ((int)r0 < lim_b ? vob[j & 1] : 0x80000000u);
-      if constexpr (KTAIL) {
-        const int row = (wid * IPW + j) * RPI + lane / CPR;
+        const int row = (wid * IPH + j) * RPI + lane / CPR;
         const uint32_t ck = kb + (((lane % CPR) ^ swz(row)) * 16);
         if ((int64_t)ck >= Kb) o = 0x80000000u;
       }
-      if (op_a)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsa, LDSP(smem + off_a(kt) + (wid * IPW + j) * 1024), 16, o,
-                                                 kb + r0 * lda_b, 0, 0);
-      else
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsb, LDSP(smem + off_b(kt) + (wid * IPW + j) * 1024), 16, o,
-                                                 kb + r0 * ldb_b, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rs, LDSP(smem + (op_b ? OPND_B : 0) + (buf * 2 + h) * HALF_B + (wid * IPH + j) * 1024), 16, o,
+          kb + (uint32_t)(h * HALF + (wid * IPH + j) * RPI) * (op_b ? ldb_b : lda_b), 0, 0);
     }
   };
-  // Fragment reads: lane (lrow, lh) takes logical K chunk 2 kk + lh of row r.
-  auto frags = [&](int kt, int kk, u32x4 (&fa)[MBW], u32x4 (&fb)[NBW]) {
-    const char* sA = smem + off_a(kt);
-    const char* sB = smem + off_b(kt);
+  // Fragment reads: lane (lr, lg) takes logical K chunk 4 kk + lg of row lr of each 16-row block.
+  const int rd_a = (wm * WTM + lr) * KS, rd_b = OPND_B + (wn * WTN + lr) * KS;
+  const int ch0 = (lg ^ swz(lr)) * 16, ch1 = ((4 + lg) ^ swz(lr)) * 16;
+  u32x4 fa[MB][2], fb[2][NB][2];
+  auto read_a = [&](int buf, int h) {
 #pragma unroll
-    for (int mb = 0; mb < MBW; ++mb) {
-      const int r = wm * WTM + mb * 32 + lrow;
-      fa[mb] = *reinterpret_cast<const u32x4*>(sA + r * KS + (((2 * kk + lh) ^ swz(r)) * 16));
-    }
+    for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-    for (int nb = 0; nb < NBW; ++nb) {
-      const int r = wn * WTN + nb * 32 + lrow;
-      fb[nb] = *reinterpret_cast<const u32x4*>(sB + r * KS + (((2 * kk + lh) ^ swz(r)) * 16));
-    }
+      for (int mb = 0; mb < MB; ++mb)
+        fa[mb][kk] = *reinterpret_cast<const u32x4*>(smem + rd_a + (kk ? ch1 : ch0) + (buf * 2 + h) * HALF_B +
+                                                     mb * 16 * KS);
   };
-
-  f32x16 acc[MBW][NBW];
+  auto read_b = [&](int buf, int h) {
 #pragma unroll
-  for (int i = 0; i < MBW; ++i)
+    for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-    for (int j = 0; j < NBW; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-  auto mma = [&](const u32x4 (&fa)[MBW], const u32x4 (&fb)[NBW]) {
-#pragma unroll
-    for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NBW; ++nb) Op<T>::mma(acc[mb][nb], fa[mb], fb[nb]);
+      for (int nb = 0; nb < NB; ++nb)
+        fb[h][nb][kk] = *reinterpret_cast<const u32x4*>(smem + rd_b + (kk ? ch1 : ch0) + (buf * 2 + h) * HALF_B +
+                                                        nb * 16 * KS);
   };
 
-  // Pipeline over K slices with NSTAGE LDS buffers: the copy of slice kt + NSTAGE is issued
-  // right after the barrier that retires slice kt, so every copy has NSTAGE - 1 slices of MFMA
-  // work to land.  Within a slice, the fragments of K step kk + 1 are read under the MFMAs of
-  // step kk; at the last step this wave's copies of slice kt + 1 are awaited, one barrier
-  // publishes every wave's copies (and retires slice kt), slice kt + NSTAGE is issued into the
-  // freed buffer and the first fragments of slice kt + 1 are read.
-  u32x4 f0a[MBW], f0b[NBW], f1a[MBW], f1b[NBW];
-  if constexpr (DEEP_B) {
-    // Three-stage B: at the end of slice kt the A copies of slice kt + 2 and then the B copies of slice
-    // kt + 3 are issued, so when slice kt + 1 is awaited only the newest B batch may still be in flight.
-    if (nk > 0) {
-      dma_op(true, 0);
-      dma_op(false, 0);
-    }
-    if (nk > 1) {
-      dma_op(true, 1);
-      dma_op(false, 1);
-    }
-    if (nk > 2) dma_op(false, 2);
-    if (nk > 0) {
-      if (nk > 2) wait_vmcnt<3 * IPW>();
-      else wait_vmcnt<0>();
-      block_barrier();
-      frags(0, 0, f0a, f0b);
-    }
-  } else {
-    const int npro = min(nk, NSTAGE);
-    for (int s = 0; s < npro; ++s) dma(s);
-    if (nk > 0) {
-      wait_vmcnt_dyn(DMA_PER_SLICE * (npro - 1));
-      block_barrier();
-      frags(0, 0, f0a, f0b);
-    }
-  }
-  // steady state: every copy the loop issues lies inside [0, nk)
-  const int ahead = DEEP_B ? 3 : NSTAGE;
-  int kt = 0;
-  for (; kt + ahead < nk; ++kt) {
+  f32x4 acc[2][2][MB][NB];
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) {
-      u32x4(&ca)[MBW] = (kk & 1) ? f1a : f0a;
-      u32x4(&cb)[NBW] = (kk & 1) ? f1b : f0b;
-      u32x4(&na)[MBW] = (kk & 1) ? f0a : f1a;
-      u32x4(&nb)[NBW] = (kk & 1) ? f0b : f1b;
-      if (kk + 1 < NKK) {
-        frags(kt, kk + 1, na, nb);
-        mma(ca, cb);
-        sched_step<MBW * NBW, MBW + NBW, 0>();
-      } else {
-        if constexpr (DEEP_B) wait_vmcnt<IPW>();  // slice kt+1 has landed; B of slice kt+2 may be in flight
-        else wait_vmcnt<DMA_PER_SLICE * (NSTAGE - 2)>();  // slice kt+1 has landed
-        wait_lgkm0();
-        block_barrier();
-        if constexpr (DEEP_B) {
-          dma_op(true, kt + 2);
-          dma_op(false, kt + 3);
-        } else {
-          dma(kt + NSTAGE);
-        }
-        frags(kt + 1, 0, na, nb);
-        mma(ca, cb);
-        sched_step<MBW * NBW, MBW + NBW, DMA_PER_SLICE>();
-      }
-    }
-  }
-  for (; kt < nk; ++kt) {
-    // drain: the last copies (DEEP_B: the A copies of the last slice), no interleaving
+  for (int i = 0; i < 4 * MB * NB; ++i) acc[i / (2 * MB * NB)][i / (MB * NB) % 2][i / NB % MB][i % NB] = f32x4{0, 0, 0, 0};
+  // one quadrant of one slice: 16 MFMAs
+  auto mma = [&](int ha, int hb) {
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) {
-      u32x4(&ca)[MBW] = (kk & 1) ? f1a : f0a;
-      u32x4(&cb)[NBW] = (kk & 1) ? f1b : f0b;
-      u32x4(&na)[MBW] = (kk & 1) ? f0a : f1a;
-      u32x4(&nb)[NBW] = (kk & 1) ? f0b : f1b;
-      if (kk + 1 < NKK) {
-        frags(kt, kk + 1, na, nb);
-      } else if (kt + 1 < nk) {
-        if constexpr (DEEP_B) wait_vmcnt<0>();
-        else wait_vmcnt_dyn(DMA_PER_SLICE * min(nk - 2 - kt, NSTAGE - 2));
-        wait_lgkm0();
-        block_barrier();
-        if constexpr (DEEP_B) {
-          if (kt + 2 < nk) dma_op(true, kt + 2);
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          if constexpr (EPI == EPI_FWD) Op<T>::mma(acc[ha][hb][mb][nb], fa[mb][kk], fb[hb][nb][kk]);
+          else Op<T>::mma(acc[ha][hb][mb][nb], fb[hb][nb][kk], fa[mb][kk]);
         }
-        frags(kt + 1, 0, na, nb);
-      }
-      mma(ca, cb);
-    }
+    __builtin_amdgcn_s_setprio(0);
+  };
+
+  // Main loop.  A slice takes four phases, one quadrant each: (A0, B0), (A0, B1), (A1, B0), (A1, B1).  A
+  // phase of a wavefront is a memory step (fragment reads of the operand half that the phase needs
+  // first, the copies of one half tile, a wait for the half tile that the next phase reads), a barrier,
+  // the 16 MFMAs, and a barrier.  The wavefronts of wm = 1 run one barrier behind those of wm = 0, and
+  // the two of a SIMD are of different wm: while one runs its MFMAs the other does its memory step.
+  //   A half tile read in phase p is safe to overwrite from the memory step of phase p + 2 on: by then
+  // the wavefronts of both groups have waited for their reads (after phase p's barrier) and passed
+  // another barrier.  Half tiles are therefore copied in the order B0 A0 B1 A1, two slices ahead, one
+  // per phase, and every copy has five phases (1.25 slices) to land: with two copies per half tile, the
+  // wait leaves 10 in flight.  B0 of the next slice is read in the last phase of a slice, so the phases
+  // read 8, 4, 8 and 4 fragments.
+  //   Bound by the matrix cores' power: at 16,384-row chunks and up dhidden and dW keep them busy 86-88 %
+  // of the cycles at 1.6 GHz.  Against one barrier and one burst of copies per slice (32 x 32 MFMAs, every
+  // copy one slice ahead), d = 4096, V = 151,936, 211,143 tokens: forward 218 -> 193 ms, dhidden 177 ->
+  // 155 ms, dW 177 -> 153 ms.  Issuing the copies before the fragment reads costs 5-10 %; raising the
+  // copies' lead to six phases, or leaving out s_setprio, changes nothing.
+  constexpr int IN_FLIGHT = 5 * IPH;
+  copy_half(true, 0, 0, 0);
+  copy_half(false, 0, 0, 0);
+  copy_half(true, 1, 0, 0);
+  copy_half(false, 1, 0, 0);
+  copy_half(true, 0, 1, 1);
+  copy_half(false, 0, 1, 1);
+  copy_half(true, 1, 1, 1);
+  wait_vmcnt<IN_FLIGHT>();
+  block_barrier();
+  read_b(0, 0);
+  if (wm == 1) block_barrier();
+  auto slice = [&](int kt, auto BUF) {
+    constexpr int buf = decltype(BUF)::value;
+    read_a(buf, 0);
+    copy_half(false, 1, kt + 1, buf ^ 1);
+    wait_vmcnt<IN_FLIGHT>();
+    block_barrier();
+    wait_lgkm0();
+    mma(0, 0);
+    block_barrier();
+    read_b(buf, 1);
+    copy_half(true, 0, kt + 2, buf);
+    wait_vmcnt<IN_FLIGHT>();
+    block_barrier();
+    wait_lgkm0();
+    mma(0, 1);
+    block_barrier();
+    read_a(buf, 1);
+    copy_half(false, 0, kt + 2, buf);
+    wait_vmcnt<IN_FLIGHT>();
+    block_barrier();
+    wait_lgkm0();
+    mma(1, 0);
+    block_barrier();
+    read_b(buf ^ 1, 0);
+    copy_half(true, 1, kt + 2, buf);
+    wait_vmcnt<IN_FLIGHT>();
+    block_barrier();
+    wait_lgkm0();
+    mma(1, 1);
+    block_barrier();
+  };
+  for (int kt = 0; kt < nk; kt += 2) {
+    slice(kt, std::integral_constant<int, 0>{});
+    if (kt + 1 < nk) slice(kt + 1, std::integral_constant<int, 1>{});
   }
+  if (wm == 0) block_barrier();
   // the epilogues reuse the LDS of the pipeline
+  wait_vmcnt<0>();
   wait_lgkm0();
   block_barrier();
 
   // ------------------------------------------------------------------ epilogues
-  // Accumulator (mb, nb, r) of this lane sits at tile row wm*WTM + mb*32 + 8*(r/4) + 4*lh + r%4 and
-  // tile column wn*WTN + nb*32 + lrow.
   if constexpr (EPI != EPI_FWD) {
-    if (a.ksplit > 1) {
-      // split K: fp32 partial of this K range; the reduction kernel applies the epilogue
-      float* part = a.part + (int64_t)blockIdx.y * a.mp * a.ldp;
+    // rows (tokens of the chunk, or vocabulary) of this lane's accumulators: tile row
+    // ha*HALF + wm*WTM + mb*16 + lr; columns (features): hb*HALF + wn*WTN + nb*16 + 4*lg + 0..3.
+    // N is a multiple of 8, so a group of four columns is inside or outside as a whole.
+    const int row0 = tile_m * kTile + wm * WTM + lr, col0 = tile_n * kTile + wn * WTN + 4 * lg;
+    auto half_rows = [&](auto FULL, int ha, auto&& f) {
 #pragma unroll
-      for (int mb = 0; mb < MBW; ++mb)
+      for (int mb = 0; mb < MB; ++mb) {
+        const int rl = row0 + ha * HALF + mb * 16;
+        if (decltype(FULL)::value || rl < M) f(ha, mb, rl);
+      }
+    };
+    auto rows = [&](auto FULL, auto&& f) {
+      half_rows(FULL, 0, f);
+      half_rows(FULL, 1, f);
+    };
+    auto cols = [&](auto FULL, auto&& f) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int rl = tile_m * kTile + wm * WTM + mb * 32 + (r >> 2) * 8 + lh * 4 + (r & 3);
-          if (rl < M) {
+      for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
-            for (int nb = 0; nb < NBW; ++nb) {
-              const int cl = tile_n * kTile + wn * WTN + nb * 32 + lrow;
-              if (cl < N) part[(int64_t)rl * a.ldp + cl] = acc[mb][nb][r];
-            }
-          }
+        for (int nb = 0; nb < NB; ++nb) {
+          const int cl = col0 + hb * HALF + nb * 16;
+          if (decltype(FULL)::value || cl < N) f(hb, nb, cl);
         }
-      return;
-    }
-  }
-  if constexpr (EPI == EPI_FWD) {
-    // rows = vocabulary v = v0 + rl, columns = chunk-local token n.  Logits z = (W h) / tau.
+    };
+    auto emit = [&](auto FULL) {
+      if (a.ksplit > 1) {
+        // split K: fp32 partial of this K range; the reduction kernel applies the epilogue
+        float* part = a.part + (int64_t)blockIdx.y * a.mp * a.ldp;
+        rows(FULL, [&](int ha, int mb, int rl) {
+          cols(FULL, [&](int hb, int nb, int cl) { store4(part + (int64_t)rl * a.ldp + cl, acc[ha][hb][mb][nb]); });
+        });
+      } else if constexpr (EPI == EPI_DH) {
+        // scatter to dh[idx[c0 + row]]; with row scales (token-reference layout), dh = diag(s) (q W^T)
+        T* out = reinterpret_cast<T*>(a.out);
+        const bool scaled = a.rs != nullptr && *a.rs_off == 0;
+        int64_t row[2][MB];
+        float sc[2][MB];
+        rows(FULL, [&](int ha, int mb, int rl) {
+          row[ha][mb] = a.idx[a.c0 + rl];
+          sc[ha][mb] = scaled ? a.rs[rl] : 1.0f;
+        });
+        rows(FULL, [&](int ha, int mb, int rl) {
+          cols(FULL, [&](int hb, int nb, int cl) {
+            store4(out + row[ha][mb] * a.ldo + cl, acc[ha][hb][mb][nb] * sc[ha][mb]);
+          });
+        });
+      } else {
+        // dW is overwritten by the first chunk unless the caller accumulates; dW may be aligned to its
+        // elements only
+        const bool wide = (reinterpret_cast<uintptr_t>(a.dw) & 15) == 0;
+        const bool add = a.accumulate || a.c0 > 0;
+#pragma unroll
+        for (int ha = 0; ha < 2; ++ha) {
+          // the 16 loads of a half are in flight together; those of both halves would not fit the
+          // registers
+          if (wide && add)
+            half_rows(FULL, ha, [&](int, int mb, int rl) {
+              cols(FULL, [&](int hb, int nb, int cl) {
+                acc[ha][hb][mb][nb] += *reinterpret_cast<const f32x4*>(a.dw + (int64_t)rl * a.ldo + cl);
+              });
+            });
+          half_rows(FULL, ha, [&](int, int mb, int rl) {
+            cols(FULL, [&](int hb, int nb, int cl) {
+              float* p = a.dw + (int64_t)rl * a.ldo + cl;
+              if (wide) {
+                store4(p, acc[ha][hb][mb][nb]);
+              } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) p[r] = add ? p[r] + acc[ha][hb][mb][nb][r] : acc[ha][hb][mb][nb][r];
+              }
+            });
+          });
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    };
+    if (rows_a == kTile && rows_b == kTile) emit(std::true_type{});
+    else emit(std::false_type{});
+  } else {
+    // rows = vocabulary v = v0 + rl with rl = ha*HALF + wm*WTM + mb*16 + 4*lg + r, columns =
+    // chunk-local token n, tile column hb*HALF + wn*WTN + nb*16 + lr.  Logits z = (W h) / tau.
     if (a.inv_tau != 1.0f) {
 #pragma unroll
-      for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < NBW; ++nb) acc[mb][nb] *= a.inv_tau;
+      for (int i = 0; i < 4 * MB * NB; ++i) acc[i / (2 * MB * NB)][i / (MB * NB) % 2][i / NB % MB][i % NB] *= a.inv_tau;
     }
     const int v0 = tile_m * kTile;
     const int V = a.V;
@@ -497,30 +463,32 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
 
     // phase 1: per-token max over this tile's 256 vocabulary rows; gather the target logit.
 #pragma unroll
-    for (int nb = 0; nb < NBW; ++nb) {
-      const int cl = wn * WTN + nb * 32 + lrow;
+    for (int cb = 0; cb < 2 * NB; ++cb) {
+      const int hb = cb / NB, nb = cb % NB;
+      const int cl = hb * HALF + wn * WTN + nb * 16 + lr;
       const int n = tile_n * kTile + cl;
       float mx = -INFINITY;
 #pragma unroll
-      for (int mb = 0; mb < MBW; ++mb)
+      for (int rb = 0; rb < 2 * MB; ++rb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int rl = wm * WTM + mb * 32 + (r >> 2) * 8 + lh * 4 + (r & 3);
-          const float z = (full_v || v0 + rl < V) ? acc[mb][nb][r] : -INFINITY;
+        for (int r = 0; r < 4; ++r) {
+          const int rl = (rb / MB) * HALF + wm * WTM + (rb % MB) * 16 + 4 * lg + r;
+          const float z = (full_v || v0 + rl < V) ? acc[rb / MB][hb][rb % MB][nb][r] : -INFINITY;
           mx = fmaxf(mx, z);
         }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      if (lh == 0) red_m[wm * kTile + cl] = mx;
+      if (lg == 0) red_m[wm * kTile + cl] = mx;
       if (n < N) {
         const int y = a.ytgt[a.c0 + n];
-        const int yl = y - v0 - wm * WTM;
-        if (y >= 0 && y < V && yl >= 0 && yl < WTM && ((yl >> 2) & 1) == lh) {
-          const int tmb = yl >> 5, tr = ((yl & 31) >> 3) * 4 + (yl & 3);
+        const int yl = y - v0;
+        if (y >= 0 && y < V && yl >= 0 && yl < kTile && ((yl / WTM) & 1) == wm && ((yl >> 2) & 3) == lg) {
+          const int trb = (yl / HALF) * MB + (yl % WTM) / 16, tr = yl & 3;
           float z = 0.0f;
 #pragma unroll
-          for (int mb = 0; mb < MBW; ++mb)
+          for (int rb = 0; rb < 2 * MB; ++rb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) z = (mb == tmb && r == tr) ? acc[mb][nb][r] : z;
+            for (int r = 0; r < 4; ++r) z = (rb == trb && r == tr) ? acc[rb / MB][hb][rb % MB][nb][r] : z;
           a.zy[a.c0 + n] = z;
         }
       }
@@ -532,8 +500,9 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
     // staged for storage.
     char* sQ = smem;
 #pragma unroll
-    for (int nb = 0; nb < NBW; ++nb) {
-      const int cl = wn * WTN + nb * 32 + lrow;
+    for (int cb = 0; cb < 2 * NB; ++cb) {
+      const int hb = cb / NB, nb = cb % NB;
+      const int cl = hb * HALF + wn * WTN + nb * 16 + lr;
       float mt = red_m[cl];
 #pragma unroll
       for (int w = 1; w < WAVES_M; ++w) mt = fmaxf(mt, red_m[w * kTile + cl]);
@@ -541,50 +510,47 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
       const float mt2 = ref * kLog2e;
       float s = 0.0f, u = 0.0f;
 #pragma unroll
-      for (int mb = 0; mb < MBW; ++mb)
+      for (int rb = 0; rb < 2 * MB; ++rb) {
+        const int rl0 = (rb / MB) * HALF + wm * WTM + (rb % MB) * 16 + 4 * lg;
+        float ev[4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float ev[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int r = g * 4 + i;
-            const int rl = wm * WTM + mb * 32 + g * 8 + lh * 4 + i;
-            const float z = acc[mb][nb][r];
-            const bool valid = full_v || v0 + rl < V;
-            const float e = valid ? __builtin_amdgcn_exp2f(fmaf(z, kLog2e, -mt2)) : 0.0f;
-            s += e;
-            u = fmaf(e, z - ref, u);
-            ev[i] = e;
-          }
-          if constexpr (STORE_Q) {
-            const int rl0 = wm * WTM + mb * 32 + g * 8 + lh * 4;
-            if constexpr (sizeof(T) == 2) {
-              u32x2 pk;
-              pk.x = pack_bf16x2(ev[0], ev[1]);
-              pk.y = pack_bf16x2(ev[2], ev[3]);
-              *reinterpret_cast<u32x2*>(sQ + cl * QROW + (((rl0 >> 3) ^ qswz(cl)) << 4) + (rl0 & 7) * 2) = pk;
-            } else {
-              const int n = tile_n * kTile + cl;
-              if (n < ng) {
-                float* qp = reinterpret_cast<float*>(a.q) + (int64_t)n * a.ldq + v0 + rl0;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) qp[i] = ev[i];
-              }
+        for (int i = 0; i < 4; ++i) {
+          const float z = acc[rb / MB][hb][rb % MB][nb][i];
+          const bool valid = full_v || v0 + rl0 + i < V;
+          const float e = valid ? __builtin_amdgcn_exp2f(fmaf(z, kLog2e, -mt2)) : 0.0f;
+          s += e;
+          u = fmaf(e, z - ref, u);
+          ev[i] = e;
+        }
+        if constexpr (STORE_Q) {
+          if constexpr (sizeof(T) == 2) {
+            u32x2 pk;
+            pk.x = pack_bf16x2(ev[0], ev[1]);
+            pk.y = pack_bf16x2(ev[2], ev[3]);
+            *reinterpret_cast<u32x2*>(sQ + cl * QROW + (((rl0 >> 3) ^ qswz(cl)) << 4) + (rl0 & 7) * 2) = pk;
+          } else {
+            const int n = tile_n * kTile + cl;
+            if (n < ng) {
+              float* qp = reinterpret_cast<float*>(a.q) + (int64_t)n * a.ldq + v0 + rl0;
+              store4(qp, f32x4{ev[0], ev[1], ev[2], ev[3]});
             }
           }
         }
+      }
+      s += __shfl_xor(s, 16, 64);
+      u += __shfl_xor(u, 16, 64);
       s += __shfl_xor(s, 32, 64);
       u += __shfl_xor(u, 32, 64);
-      if (lh == 0) {
+      if (lg == 0) {
         red_s[wm * kTile + cl] = s;
         red_u[wm * kTile + cl] = u;
       }
     }
     __syncthreads();
-    if (wm == 0 && lh == 0) {
+    if (wm == 0 && lg == 0) {
 #pragma unroll
-      for (int nb = 0; nb < NBW; ++nb) {
-        const int cl = wn * WTN + nb * 32 + lrow;
+      for (int cb = 0; cb < 2 * NB; ++cb) {
+        const int cl = (cb / NB) * HALF + wn * WTN + (cb % NB) * 16 + lr;
         const int n = tile_n * kTile + cl;
         if (n < N) {
           float m = red_m[cl], s = red_s[cl], u = red_u[cl];
@@ -652,46 +618,6 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
         }
       }
     }
-  } else if constexpr (EPI == EPI_DH) {
-    // rows = chunk-local tokens, columns = hidden features; scatter to dh[idx[c0 + row]].
-    // With row scales (token-reference layout), dh = diag(s) (q W^T).
-    T* out = reinterpret_cast<T*>(a.out);
-    const bool scaled = a.rs != nullptr && *a.rs_off == 0;
-#pragma unroll
-    for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int rl = tile_m * kTile + wm * WTM + mb * 32 + (r >> 2) * 8 + lh * 4 + (r & 3);
-        if (rl < M) {
-          const int64_t row = a.idx[a.c0 + rl];
-          const float sc = scaled ? a.rs[rl] : 1.0f;
-#pragma unroll
-          for (int nb = 0; nb < NBW; ++nb) {
-            const int cl = tile_n * kTile + wn * WTN + nb * 32 + lrow;
-            if (cl < N) store_elem<T>(out + row * a.ldo + cl, acc[mb][nb][r] * sc);
-          }
-        }
-      }
-  } else {
-    // rows = vocabulary, columns = hidden features; fp32 dW, overwritten by the first
-    // chunk unless the caller accumulates.
-    const bool add = a.accumulate || a.c0 > 0;
-#pragma unroll
-    for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int rl = tile_m * kTile + wm * WTM + mb * 32 + (r >> 2) * 8 + lh * 4 + (r & 3);
-        if (rl < M) {
-#pragma unroll
-          for (int nb = 0; nb < NBW; ++nb) {
-            const int cl = tile_n * kTile + wn * WTN + nb * 32 + lrow;
-            if (cl < N) {
-              float* p = a.dw + (int64_t)rl * a.ldo + cl;
-              *p = add ? *p + acc[mb][nb][r] : acc[mb][nb][r];
-            }
-          }
-        }
-      }
   }
 }
 
@@ -714,7 +640,7 @@ __global__ void __launch_bounds__(256) k_splitk_reduce(GemmArgs a) {
     if constexpr (EPI == EPI_DH) {
       const int64_t row = a.idx[a.c0 + m];
       if (a.rs && *a.rs_off == 0) acc *= a.rs[m];
-      store_elem<T>(reinterpret_cast<T*>(a.out) + row * a.ldo + n, acc);
+      store_elem(reinterpret_cast<T*>(a.out) + row * a.ldo + n, acc);
     } else {
       float* p = a.dw + m * a.ldo + n;
       *p = add ? *p + acc : acc;

@@ -1,0 +1,59 @@
+"""Sizes at which single kernels can go wrong (tile edges, remainders, shortest and longest loops),
+against the fp64 oracle."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch  # before the library: both use the HIP runtime that torch loads
+
+from gpu_common import WL, build_instance, compare_full, ensure_library, params_for, rlk, run_gpu, run_oracle, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+def _all_policy(dtype, tokens, d, V):
+    """2 rollouts of one group, `tokens` trained tokens in all."""
+    cfg = WL.get_config("small_bf16").with_(
+        name=f"edge_{dtype}_{tokens}x{d}x{V}", dtype=dtype, groups=1, rollouts_per_group=2, len_min=tokens // 2,
+        len_max=tokens // 2, d=d, V=V, w_std=d ** -0.5)
+    st = WL.make_structure(cfg)
+    if tokens % 2:  # one more token in the last rollout
+        cu = st.cu_seqlens.copy()
+        cu[-1] += 1
+        grow = lambda a: np.concatenate([a, a[:1]])
+        st = dataclasses.replace(st, cu_seqlens=cu, lengths=np.diff(cu).astype(np.int64), targets=grow(st.targets),
+                                 noise=grow(st.noise), mask=grow(st.mask))
+    return cfg, dataclasses.replace(st, mask=np.ones_like(st.mask))
+
+
+# K slices of the forward: 1, 2, 3 (whole and with a tail); token and vocabulary tiles one short of, at and
+# one past the tile's and its halves' edges
+@pytest.mark.parametrize("dtype,tokens,d,V", [
+    ("bf16", 2, 8, 1), ("bf16", 127, 64, 129), ("bf16", 129, 72, 255), ("bf16", 255, 128, 256), ("bf16", 256, 136, 257),
+    ("bf16", 257, 192, 513), ("f32", 127, 8, 129), ("f32", 129, 32, 257), ("f32", 257, 40, 255), ("f32", 255, 96, 300)])
+@pytest.mark.parametrize("entropy", [0.0, 1e-2])
+def test_gemm_tile_edges(dtype, tokens, d, V, entropy):
+    ensure_library()
+    cfg, st = _all_policy(dtype, tokens, d, V)
+    inst = build_instance(cfg, structure=st)
+    p = params_for(cfg, entropy_coef=entropy)
+    compare_full(inst, run_gpu(inst, p), run_oracle(inst, p), p, tag="edges")
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_dw_aligned_to_its_elements_only(accumulate):
+    """dW may start at any fp32 element: the wide stores of the dW GEMM are not taken there.  The same
+    sums in the same order, so the result is that of an aligned dW."""
+    ensure_library()
+    cfg, st = _all_policy("bf16", 300, 2048, 8200)  # 33 x 8 output tiles: the GEMM itself writes dW
+    inst = build_instance(cfg, structure=st)
+    p = params_for(cfg, accumulate_dW=accumulate)
+    base = torch.randn(cfg.V * cfg.d + 1, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    out = []
+    for off in (0, 1):
+        buf = torch.empty_like(base)
+        dW = buf[off:off + cfg.V * cfg.d].view(cfg.V, cfg.d).copy_(base[:cfg.V * cfg.d].view(cfg.V, cfg.d))
+        run_gpu(inst, p, dW=dW)
+        out.append(to_host(dW))
+    np.testing.assert_array_equal(out[0], out[1])
+    assert np.isfinite(out[0]).all() and np.abs(out[0]).max() > 0
