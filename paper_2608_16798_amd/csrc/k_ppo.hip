@@ -5,107 +5,175 @@
 // GAE over a rollout's policy rows t_1 < ... < t_n (tool rows are stepped over):
 //   delta_j = gamma V[t_{j+1}] - V[t_j]  (j < n),   delta_n = R - V[t_n],
 //   A_j = delta_j + c A_{j+1}, c = gamma lambda,  returns = A + V.
-// One workgroup per rollout walks the rollout backwards in chunks of 256 rows.  Thread i of a
-// chunk holds row e - 1 - i, so increasing thread order is decreasing row order and both
-// quantities are inclusive scans over threads, carried from chunk to chunk:
+// One workgroup per rollout walks the rollout backwards, kGaeRows consecutive rows per thread and
+// pass.  Thread i holds the i-th group of rows from the end, so increasing thread order is decreasing
+// row order and both quantities are exclusive scans over threads, carried from pass to pass:
 //   - the value of the nearest later policy row (a "latest seen" scan), which gives delta;
 //   - A as the composition of the affine maps x -> (policy ? c x + delta : x).
+// Inside a wavefront the first is one ballot and one lane read, the second a shuffle scan; the
+// wavefronts meet in LDS.
 #include "rlk_internal.h"
+
+#include <algorithm>
 
 namespace rlk {
 
 namespace {
 
-constexpr int kGaeThreads = 256;
+inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+constexpr int kGaeRows = 8;    // consecutive rows per thread
 
 __device__ __forceinline__ int64_t clamp64(int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-__global__ void __launch_bounds__(kGaeThreads)
-k_gae(int64_t N, const int32_t* cu, const uint8_t* mask, const float* values, const float* rewards,
-      const int32_t* gid, float gamma, float lam, float* adv, float* ret) {
-  __shared__ int s_has[kGaeThreads];
-  __shared__ double s_val[kGaeThreads];
-  __shared__ double s_a[kGaeThreads], s_b[kGaeThreads];
-  const int r = blockIdx.x;
-  const int i = threadIdx.x;
-  const int64_t s0 = clamp64(cu[r], 0, N), s1 = clamp64(cu[r + 1], s0, N);
-  const bool excluded = gid && gid[r] < 0;
-  const double c = (double)gamma * (double)lam;
-  const double R = (double)rewards[r];
-  int carry_has = 0;        // a policy row exists after the current chunk
-  double carry_val = 0.0;   // its value
-  double carry_A = 0.0;     // advantage of the nearest policy row at or after the chunk's end
-  for (int64_t e = s1; e > s0; e -= kGaeThreads) {
-    const int64_t t = e - 1 - i;
-    const bool in = t >= s0;
-    const bool pol = in && !excluded && mask[t] != 0;
-    const double v = pol ? (double)values[t] : 0.0;
-    // (1) nearest later policy row: exclusive "latest seen" scan over threads
-    s_has[i] = pol;
-    s_val[i] = v;
-    __syncthreads();
-    for (int off = 1; off < kGaeThreads; off <<= 1) {
-      int h = 0;
-      double x = 0.0;
-      const bool take = i >= off && !s_has[i];
-      if (take) {
-        h = s_has[i - off];
-        x = s_val[i - off];
+// Rows [g, g + 8), g a multiple of 8, of the rollout's [s0, s1): bit k of the result is set where row
+// g + k belongs to it and its mask is set; v gets the values of those rows.  VEC: the array bases are
+// 16-byte aligned, so a group inside the arrays is read in three loads.
+template <bool VEC>
+__device__ __forceinline__ uint32_t load_rows(int64_t g, int64_t s0, int64_t s1, int64_t N, const uint8_t* mask,
+                                              const float* values, float (&v)[kGaeRows]) {
+  uint32_t pol = 0;
+  if (g + kGaeRows <= s0 || g >= s1) return 0;
+  if (VEC && g + kGaeRows <= N) {
+    const u32x2 m = *reinterpret_cast<const u32x2*>(mask + g);
+    const f32x4 a = *reinterpret_cast<const f32x4*>(values + g), b = *reinterpret_cast<const f32x4*>(values + g + 4);
+#pragma unroll
+    for (int k = 0; k < kGaeRows; ++k) {
+      v[k] = k < 4 ? a[k & 3] : b[k & 3];
+      if (((m[k >> 2] >> (8 * (k & 3))) & 0xffu) != 0 && g + k >= s0 && g + k < s1) pol |= 1u << k;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < kGaeRows; ++k) {
+      v[k] = 0.0f;
+      if (g + k >= s0 && g + k < s1 && mask[g + k] != 0) {
+        v[k] = values[g + k];
+        pol |= 1u << k;
       }
-      __syncthreads();
-      if (take) {
-        s_has[i] = h;
-        s_val[i] = x;
-      }
-      __syncthreads();
     }
-    int nh = carry_has;
-    double nv = carry_val;
-    if (i > 0 && s_has[i - 1]) {
-      nh = 1;
-      nv = s_val[i - 1];
-    }
-    const double delta = pol ? ((nh ? (double)gamma * nv : R) - v) : 0.0;
-    const int last_has = s_has[kGaeThreads - 1];
-    const double last_val = s_val[kGaeThreads - 1];
-    __syncthreads();
-    // (2) A: inclusive scan of the affine maps x -> a x + b over threads (thread 0 applied first)
-    double a = pol ? c : 1.0, b = pol ? delta : 0.0;
-    s_a[i] = a;
-    s_b[i] = b;
-    __syncthreads();
-    for (int off = 1; off < kGaeThreads; off <<= 1) {
-      double pa = 1.0, pb = 0.0;
-      if (i >= off) {
-        pa = s_a[i - off];
-        pb = s_b[i - off];
-      }
-      __syncthreads();
-      if (i >= off) {
-        // this map after the earlier one: x -> a (pa x + pb) + b
-        b = a * pb + b;
-        a = a * pa;
-        s_a[i] = a;
-        s_b[i] = b;
-      }
-      __syncthreads();
-    }
-    const double A = a * carry_A + b;
-    if (in) {
-      adv[t] = pol ? (float)A : 0.0f;
-      if (ret) ret[t] = pol ? (float)(A + v) : 0.0f;
-    }
-    const double chunk_a = s_a[kGaeThreads - 1], chunk_b = s_b[kGaeThreads - 1];
-    __syncthreads();
-    carry_A = chunk_a * carry_A + chunk_b;
-    if (last_has) {
-      carry_has = 1;
-      carry_val = last_val;
-    }
+  }
+  return pol;
+}
+
+// the group's rows of [s0, s1) of an output
+template <bool VEC>
+__device__ __forceinline__ void store_rows(int64_t g, int64_t s0, int64_t s1, float* out, const float (&o)[kGaeRows]) {
+  if (VEC && g >= s0 && g + kGaeRows <= s1) {
+    *reinterpret_cast<f32x4*>(out + g) = f32x4{o[0], o[1], o[2], o[3]};
+    *reinterpret_cast<f32x4*>(out + g + 4) = f32x4{o[4], o[5], o[6], o[7]};
+  } else {
+#pragma unroll
+    for (int k = 0; k < kGaeRows; ++k)
+      if (g + k >= s0 && g + k < s1) out[g + k] = o[k];
   }
 }
 
-// ---- value loss: per-rollout fp64 partial sums, one block for the totals, then the gradient.
+// Latency bound: 26 bytes per row move, and a rollout is one workgroup.  A pass takes 8 rows per
+// thread and two barriers; rollouts of up to 8 x THREADS rows take one pass.  128 rollouts of 1,024 to
+// 7,168 rows: 69 us with one row per thread, 256 rows a pass and LDS scans -> 10.4 us.
+template <bool VEC, int THREADS>
+__global__ void __launch_bounds__(THREADS)
+k_gae(int64_t N, const int32_t* cu, const uint8_t* mask, const float* values, const float* rewards,
+      const int32_t* gid, float gamma, float lam, float* adv, float* ret) {
+  constexpr int NW = THREADS / 64;
+  __shared__ int s_has[2][NW];
+  __shared__ double s_val[2][NW], s_a[2][NW], s_b[2][NW];
+  const int r = blockIdx.x;
+  const int i = threadIdx.x, lane = i & 63, w = i >> 6;
+  const int64_t s0 = clamp64(cu[r], 0, N), s1 = clamp64(cu[r + 1], s0, N);
+  const bool excluded = gid && gid[r] < 0;
+  const double c = (double)gamma * (double)lam, gam = (double)gamma;
+  const double R = (double)rewards[r];
+  bool carry_has = false;   // a policy row exists after the current pass
+  double carry_val = 0.0;   // its value
+  double carry_A = 0.0;     // advantage of the nearest policy row at or after the pass's end
+  int par = 0;
+  for (int64_t e = (s1 + kGaeRows - 1) / kGaeRows * kGaeRows; e > s0; e -= (int64_t)kGaeRows * THREADS, par ^= 1) {
+    const int64_t g = e - (int64_t)(i + 1) * kGaeRows;
+    float v[kGaeRows];
+#pragma unroll
+    for (int k = 0; k < kGaeRows; ++k) v[k] = 0.0f;
+    uint32_t pol = g >= 0 ? load_rows<VEC>(g, s0, s1, N, mask, values, v) : 0u;
+    if (excluded) pol = 0;
+    // (1) nearest later policy row: the earliest one of the nearest lower thread that has any
+    double first = 0.0;
+#pragma unroll
+    for (int k = kGaeRows - 1; k >= 0; --k)
+      if (pol >> k & 1) first = (double)v[k];
+    const uint64_t have = __ballot(pol != 0);
+    const uint64_t below = have & ((1ull << lane) - 1);
+    const double near = __shfl(first, below ? 63 - __clzll((long long)below) : 0, 64);
+    const double last = __shfl(first, have ? 63 - __clzll((long long)have) : 0, 64);
+    if (lane == 0) {
+      s_has[par][w] = have != 0;
+      s_val[par][w] = last;
+    }
+    __syncthreads();
+    bool nh = below != 0;
+    double nv = near;
+    if (!nh) {
+      nh = carry_has;
+      nv = carry_val;
+      for (int x = 0; x < w; ++x)
+        if (s_has[par][x]) {
+          nh = true;
+          nv = s_val[par][x];
+        }
+    }
+    for (int x = 0; x < NW; ++x)
+      if (s_has[par][x]) {
+        carry_has = true;
+        carry_val = s_val[par][x];
+      }
+    // (2) A: the thread's map x -> a x + b over its rows, latest row first, then the scan over threads
+    double delta[kGaeRows], a = 1.0, b = 0.0;
+#pragma unroll
+    for (int k = kGaeRows - 1; k >= 0; --k) {
+      delta[k] = 0.0;
+      if (pol >> k & 1) {
+        delta[k] = (nh ? gam * nv : R) - (double)v[k];
+        nh = true;
+        nv = (double)v[k];
+        b = c * b + delta[k];
+        a = c * a;
+      }
+    }
+    for (int off = 1; off < 64; off <<= 1) {
+      const double pa = __shfl_up(a, off, 64), pb = __shfl_up(b, off, 64);
+      if (lane >= off) {
+        b = a * pb + b;  // this map after the earlier one: x -> a (pa x + pb) + b
+        a = a * pa;
+      }
+    }
+    if (lane == 63) {
+      s_a[par][w] = a;
+      s_b[par][w] = b;
+    }
+    __syncthreads();
+    double A = carry_A;  // advantage entering the wavefront, then the thread
+    for (int x = 0; x < w; ++x) A = s_a[par][x] * A + s_b[par][x];
+    for (int x = 0; x < NW; ++x) carry_A = s_a[par][x] * carry_A + s_b[par][x];
+    const double ea = __shfl_up(a, 1, 64), eb = __shfl_up(b, 1, 64);
+    if (lane > 0) A = ea * A + eb;
+    if (g < 0 || g + kGaeRows <= s0) continue;  // no rows of this rollout (the barriers are behind)
+    float oa[kGaeRows], orr[kGaeRows];
+#pragma unroll
+    for (int k = kGaeRows - 1; k >= 0; --k) {
+      const bool p = pol >> k & 1;
+      if (p) A = c * A + delta[k];
+      oa[k] = p ? (float)A : 0.0f;
+      orr[k] = p ? (float)(A + (double)v[k]) : 0.0f;
+    }
+    store_rows<VEC>(g, s0, s1, adv, oa);
+    if (ret) store_rows<VEC>(g, s0, s1, ret, orr);
+  }
+}
+
+// ---- value loss: fp64 partial sums of (rollout, slice of its rows), their total, then the gradient.
+// A rollout's rows are cut into groups of 8 x 256 rows, dealt to kValueSplit slices, so that a batch of
+// few long rollouts still fills the GPU.  128 rollouts of 1,024 to 7,168 rows: three launches of one
+// row per thread 22.7 us -> two launches 9.8 us.
+template <bool VEC>
 __global__ void __launch_bounds__(256)
 k_value_partial(int64_t N, const int32_t* cu, const uint8_t* mask, const float* values, const float* ret,
                 const int32_t* gid, double* part) {
@@ -114,11 +182,18 @@ k_value_partial(int64_t N, const int32_t* cu, const uint8_t* mask, const float* 
   const int64_t s0 = clamp64(cu[r], 0, N), s1 = clamp64(cu[r + 1], s0, N);
   double ss = 0.0, cnt = 0.0;
   if (!(gid && gid[r] < 0)) {
-    for (int64_t t = s0 + threadIdx.x; t < s1; t += 256) {
-      if (!mask[t]) continue;
-      const double d = (double)values[t] - (double)ret[t];
-      ss += d * d;
-      cnt += 1.0;
+    for (int64_t g = s0 / kGaeRows * kGaeRows + ((int64_t)blockIdx.y * 256 + threadIdx.x) * kGaeRows; g < s1;
+         g += (int64_t)gridDim.y * 256 * kGaeRows) {
+      float v[kGaeRows], t[kGaeRows];
+      const uint32_t pol = load_rows<VEC>(g, s0, s1, N, mask, values, v);
+      load_rows<VEC>(g, s0, s1, N, mask, ret, t);
+#pragma unroll
+      for (int k = 0; k < kGaeRows; ++k)
+        if (pol >> k & 1) {
+          const double d = (double)v[k] - (double)t[k];
+          ss += d * d;
+          cnt += 1.0;
+        }
     }
   }
   for (int o = 32; o > 0; o >>= 1) {
@@ -130,14 +205,17 @@ k_value_partial(int64_t N, const int32_t* cu, const uint8_t* mask, const float* 
     sh[threadIdx.x >> 6][1] = cnt;
   }
   __syncthreads();
-  if (threadIdx.x < 2) part[(int64_t)r * 2 + threadIdx.x] = sh[0][threadIdx.x] + sh[1][threadIdx.x] +
-                                                             sh[2][threadIdx.x] + sh[3][threadIdx.x];
+  if (threadIdx.x < 2)
+    part[((int64_t)r * gridDim.y + blockIdx.y) * 2 + threadIdx.x] =
+        sh[0][threadIdx.x] + sh[1][threadIdx.x] + sh[2][threadIdx.x] + sh[3][threadIdx.x];
 }
 
-__global__ void __launch_bounds__(1024) k_value_final(int R, const double* part, double* total, float* loss) {
-  __shared__ double sh[16][2];
+// total of n partials in a fixed order (the same in every block that forms it)
+template <int THREADS>
+__device__ __forceinline__ void value_total(int n, const double* part, double& sum, double& count) {
+  __shared__ double sh[THREADS / 64][2];
   double ss = 0.0, cnt = 0.0;
-  for (int r = threadIdx.x; r < R; r += 1024) {
+  for (int r = threadIdx.x; r < n; r += THREADS) {
     ss += part[(int64_t)r * 2];
     cnt += part[(int64_t)r * 2 + 1];
   }
@@ -150,27 +228,49 @@ __global__ void __launch_bounds__(1024) k_value_final(int R, const double* part,
     sh[threadIdx.x >> 6][1] = cnt;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double a = 0.0, n = 0.0;
-    for (int k = 0; k < 16; ++k) {
-      a += sh[k][0];
-      n += sh[k][1];
-    }
-    total[0] = n;
-    loss[0] = n > 0 ? (float)(a / n) : 0.0f;
+  sum = 0.0;
+  count = 0.0;
+  for (int k = 0; k < THREADS / 64; ++k) {
+    sum += sh[k][0];
+    count += sh[k][1];
   }
 }
 
+__global__ void __launch_bounds__(1024) k_value_final(int n, const double* part, double* total, float* loss) {
+  double a, cnt;
+  value_total<1024>(n, part, a, cnt);
+  if (threadIdx.x == 0) {
+    total[0] = cnt;
+    loss[0] = cnt > 0 ? (float)(a / cnt) : 0.0f;
+  }
+}
+
+// With npart > 0 every block adds up the partials itself (and block 0 writes the loss), which saves the
+// launch of k_value_final; otherwise the count is in total.
+template <bool VEC>
 __global__ void __launch_bounds__(256)
 k_value_grad(int64_t N, const int32_t* cu, const uint8_t* mask, const float* values, const float* ret,
-             const int32_t* gid, const double* total, float* dv) {
+             const int32_t* gid, int npart, const double* part, const double* total, float* loss, float* dv) {
   const int r = blockIdx.x;
+  double n;
+  if (npart > 0) {
+    double sum;
+    value_total<256>(npart, part, sum, n);
+    if (r == 0 && blockIdx.y == 0 && threadIdx.x == 0) loss[0] = n > 0 ? (float)(sum / n) : 0.0f;
+  } else {
+    n = total[0];
+  }
   const int64_t s0 = clamp64(cu[r], 0, N), s1 = clamp64(cu[r + 1], s0, N);
-  const bool excluded = gid && gid[r] < 0;
-  const double n = total[0];
-  for (int64_t t = s0 + threadIdx.x; t < s1; t += 256) {
-    const bool on = !excluded && mask[t] && n > 0;
-    dv[t] = on ? (float)(2.0 * ((double)values[t] - (double)ret[t]) / n) : 0.0f;
+  const bool on = !(gid && gid[r] < 0) && n > 0;
+  for (int64_t g = s0 / kGaeRows * kGaeRows + ((int64_t)blockIdx.y * 256 + threadIdx.x) * kGaeRows; g < s1;
+       g += (int64_t)gridDim.y * 256 * kGaeRows) {
+    float v[kGaeRows], t[kGaeRows], o[kGaeRows];
+    const uint32_t pol = load_rows<VEC>(g, s0, s1, N, mask, values, v);
+    load_rows<VEC>(g, s0, s1, N, mask, ret, t);
+#pragma unroll
+    for (int k = 0; k < kGaeRows; ++k)
+      o[k] = on && (pol >> k & 1) ? (float)(2.0 * ((double)v[k] - (double)t[k]) / n) : 0.0f;
+    store_rows<VEC>(g, s0, s1, dv, o);
   }
 }
 
@@ -411,8 +511,13 @@ hipError_t launch_value_head_bwd(int dtype, int64_t N, int d, int R, const void*
 hipError_t launch_gae(int64_t N, int R, const int32_t* cu, const uint8_t* mask, const float* values,
                       const float* rewards, const int32_t* gid, float gamma, float lam, float* adv, float* ret,
                       hipStream_t s) {
+  // Long rollouts get a workgroup that covers 8,192 rows in one pass; short ones leave its barriers and
+  // wavefronts idle and get the small one (the mean length decides; either is right for any length).
   prof_mark(KK_GAE, true, s);
-  k_gae<<<R, kGaeThreads, 0, s>>>(N, cu, mask, values, rewards, gid, gamma, lam, adv, ret);
+  const bool vec = aligned16(mask) && aligned16(values) && aligned16(adv) && aligned16(ret);
+  const bool big = N / R > 1024;
+  auto* k = big ? (vec ? k_gae<true, 1024> : k_gae<false, 1024>) : (vec ? k_gae<true, 256> : k_gae<false, 256>);
+  k<<<R, big ? 1024 : 256, 0, s>>>(N, cu, mask, values, rewards, gid, gamma, lam, adv, ret);
   prof_mark(KK_GAE, false, s);
   return hipGetLastError();
 }
@@ -421,9 +526,18 @@ hipError_t launch_value_loss(int64_t N, int R, const int32_t* cu, const uint8_t*
                              const float* ret, const int32_t* gid, double* part, double* total, float* loss,
                              float* dv, hipStream_t s) {
   prof_mark(KK_VALUE_LOSS, true, s);
-  k_value_partial<<<R, 256, 0, s>>>(N, cu, mask, values, ret, gid, part);
-  k_value_final<<<1, 1024, 0, s>>>(R, part, total, loss);
-  if (dv) k_value_grad<<<R, 256, 0, s>>>(N, cu, mask, values, ret, gid, total, dv);
+  const bool vec = aligned16(mask) && aligned16(values) && aligned16(ret) && aligned16(dv);
+  // slices per rollout: one per 2,048 rows of the mean length, as many as the workspace holds
+  const int ny = (int)std::min<int64_t>(std::max<int64_t>(R > 0 ? N / R / 2048 : 1, 1), kValueSplit);
+  const dim3 grid(R, ny);
+  const int np = R * ny;
+  (vec ? k_value_partial<true> : k_value_partial<false>)<<<grid, 256, 0, s>>>(N, cu, mask, values, ret, gid, part);
+  // up to 1,024 partials the gradient's blocks add them up themselves (four loads per thread)
+  const bool own_total = dv && np <= 1024;
+  if (!own_total) k_value_final<<<1, 1024, 0, s>>>(np, part, total, loss);
+  if (dv)
+    (vec ? k_value_grad<true> : k_value_grad<false>)<<<grid, 256, 0, s>>>(N, cu, mask, values, ret, gid, own_total ? np : 0,
+                                                                          part, total, loss, dv);
   prof_mark(KK_VALUE_LOSS, false, s);
   return hipGetLastError();
 }

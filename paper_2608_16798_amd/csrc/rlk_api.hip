@@ -938,7 +938,7 @@ rlk_status_t rlk_value_workspace_size(int32_t R, size_t* bytes) {
   Alloc a;
   a.take(sizeof(WsHeader));
   a.take(sizeof(double) * 2);
-  a.take((size_t)R * 16);
+  a.take((size_t)R * kValueSplit * 16);
   *bytes = a.off;
   return RLK_OK;
 }
@@ -960,7 +960,7 @@ rlk_status_t rlk_value_loss(int64_t N, int32_t R, const int32_t* cu_seqlens, con
   char* w = static_cast<char*>(ws);
   a.take(sizeof(WsHeader));
   double* total = reinterpret_cast<double*>(w + a.take(sizeof(double) * 2));
-  double* part = reinterpret_cast<double*>(w + a.take((size_t)R * 16));
+  double* part = reinterpret_cast<double*>(w + a.take((size_t)R * kValueSplit * 16));
   RLK_TRY(launch_value_loss(N, R, cu_seqlens, mask, values, returns, group_ids, part, total, loss, dvalues, s),
           "value_loss");
   return RLK_OK;

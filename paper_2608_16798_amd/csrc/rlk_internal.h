@@ -252,6 +252,7 @@ hipError_t launch_value_loss(int64_t N, int R, const int32_t* cu, const uint8_t*
                              const float* ret, const int32_t* gid, double* part, double* total, float* loss,
                              float* dv, hipStream_t s);
 
+constexpr int kValueSplit = 4;  // most slices of a rollout in the value loss (2 doubles of workspace each)
 size_t value_head_workspace(int64_t N, int d);
 hipError_t launch_value_head_fwd(int dtype, int64_t N, int d, int R, const void* h, const void* w, float b,
                                  const uint8_t* mask, const int32_t* cu, const int32_t* gid, float* values,

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch  # before the library: both use the HIP runtime that torch loads
 
-from gpu_common import WL, build_instance, compare_full, ensure_library, params_for, rlk, run_gpu, run_oracle, to_host
+from gpu_common import O, WL, build_instance, compare_full, ensure_library, params_for, rlk, run_gpu, run_oracle, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +57,50 @@ def test_dw_aligned_to_its_elements_only(accumulate):
         out.append(to_host(dW))
     np.testing.assert_array_equal(out[0], out[1])
     assert np.isfinite(out[0]).all() and np.abs(out[0]).max() > 0
+
+
+# one pass takes 8 rows per thread of 256 or 1,024 threads (short and long mean length); groups of 8 rows
+# straddle the rollouts; off = 1 starts the arrays at an element that is not 16-byte aligned
+@pytest.mark.parametrize("lens", [(0, 1, 7, 8, 9, 15, 17), (2047, 2048, 2049, 3, 0, 1), (8191, 5, 8193, 8192), (20001, 1)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_gae_and_value_loss_row_groups(lens, off):
+    ensure_library()
+    rng = np.random.default_rng(len(lens) + off)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    N, R = int(cu[-1]), len(lens)
+    mask = (rng.random(N) < 0.4).astype(np.uint8)
+    vals, rew = rng.standard_normal(N).astype(np.float32), rng.standard_normal(R).astype(np.float32)
+    gid = np.arange(R, dtype=np.int32)
+    gid[1] = -1
+
+    def dev(a):
+        buf = torch.empty(a.shape[0] + off, dtype=torch.as_tensor(a).dtype, device="cuda")
+        buf[off:].copy_(torch.as_tensor(a))
+        return buf[off:]
+
+    v, m, c, g = dev(vals), dev(mask), torch.as_tensor(cu, device="cuda"), torch.as_tensor(gid, device="cuda")
+    out = [dev(np.full(N, np.nan, np.float32)) for _ in range(3)]
+    adv, ret = rlk.gae(v, torch.as_tensor(rew, device="cuda"), m, c, g, 0.99, 0.95, adv=out[0], returns=out[1])
+    loss, dv = rlk.value_loss(v, ret, m, c, g, dvalues=out[2])
+    # the C entry takes gamma and lambda as fp32; fp64 scans, one rounding to fp32
+    ra, rr = O.gae(vals, rew, mask, cu, gid, float(np.float32(0.99)), float(np.float32(0.95)))
+    np.testing.assert_allclose(to_host(adv), ra, rtol=0, atol=2e-7 * np.abs(ra).max())
+    np.testing.assert_allclose(to_host(ret), rr, rtol=0, atol=2e-7 * np.abs(rr).max())
+    rl, rdv = O.value_loss(vals, to_host(ret), mask, cu, gid)
+    assert abs(float(loss.item()) - rl) <= 2e-7 * abs(rl)
+    np.testing.assert_allclose(to_host(dv), rdv, rtol=0, atol=2e-7 * np.abs(rdv).max())
+
+
+def test_value_loss_of_many_rollouts():
+    """More partial sums than the gradient's workgroups add up by themselves (1,024)."""
+    ensure_library()
+    rng = np.random.default_rng(5)
+    R = 1500
+    cu = np.concatenate([[0], np.cumsum(rng.integers(0, 12, R))]).astype(np.int32)
+    N = int(cu[-1])
+    mask, vals, rets = (rng.random(N) < 0.5).astype(np.uint8), rng.standard_normal(N).astype(np.float32), rng.standard_normal(N).astype(np.float32)
+    d = lambda a: torch.as_tensor(a, device="cuda")
+    loss, dv = rlk.value_loss(d(vals), d(rets), d(mask), d(cu))
+    rl, rdv = O.value_loss(vals, rets, mask, cu)
+    assert abs(float(loss.item()) - rl) <= 2e-7 * abs(rl)
+    np.testing.assert_allclose(to_host(dv), rdv, rtol=0, atol=2e-7 * np.abs(rdv).max())
