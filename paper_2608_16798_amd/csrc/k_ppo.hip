@@ -126,16 +126,14 @@ k_gae(int64_t N, const int32_t* cu, const uint8_t* mask, const float* values, co
         carry_val = s_val[par][x];
       }
     // (2) A: the thread's map x -> a x + b over its rows, latest row first, then the scan over threads
-    double delta[kGaeRows], a = 1.0, b = 0.0;
+    const double next0 = nh ? gam * nv : R;  // gamma V of the next policy row, or the reward
+    double next = next0, a = 1.0, b = 0.0;
 #pragma unroll
     for (int k = kGaeRows - 1; k >= 0; --k) {
-      delta[k] = 0.0;
       if (pol >> k & 1) {
-        delta[k] = (nh ? gam * nv : R) - (double)v[k];
-        nh = true;
-        nv = (double)v[k];
-        b = c * b + delta[k];
+        b = c * b + (next - (double)v[k]);
         a = c * a;
+        next = gam * (double)v[k];
       }
     }
     for (int off = 1; off < 64; off <<= 1) {
@@ -157,10 +155,14 @@ k_gae(int64_t N, const int32_t* cu, const uint8_t* mask, const float* values, co
     if (lane > 0) A = ea * A + eb;
     if (g < 0 || g + kGaeRows <= s0) continue;  // no rows of this rollout (the barriers are behind)
     float oa[kGaeRows], orr[kGaeRows];
+    next = next0;
 #pragma unroll
     for (int k = kGaeRows - 1; k >= 0; --k) {
       const bool p = pol >> k & 1;
-      if (p) A = c * A + delta[k];
+      if (p) {
+        A = c * A + (next - (double)v[k]);
+        next = gam * (double)v[k];
+      }
       oa[k] = p ? (float)A : 0.0f;
       orr[k] = p ? (float)(A + (double)v[k]) : 0.0f;
     }
@@ -314,14 +316,40 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
   return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)lo) | ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)hi) << 16);
 }
 
-constexpr int kHeadRows = 256;    // rows per workgroup of the dW partial sums
+constexpr int kHeadRows = 128;    // rows per workgroup of the backward
 
-// one wavefront per row
+// The kept ones of the ROWS rows from t0 on, in row order, listed in LDS by the first ROWS threads (every
+// thread of the workgroup calls it); returns their number, and in keep whether the thread's own row is one.
+template <int ROWS>
+__device__ __forceinline__ int list_kept(int64_t t0, int64_t N, const uint8_t* mask, const int32_t* cu,
+                                         const int32_t* gid, int R, int16_t (&list)[ROWS], bool& keep) {
+  static_assert(ROWS % 64 == 0, "whole ballots");
+  __shared__ int count[ROWS / 64];
+  const int i = threadIdx.x;
+  keep = i < ROWS && t0 + i < N && kept_row(mask, cu, gid, R, t0 + i);
+  const uint64_t b = __ballot(keep);
+  if (i < ROWS && (i & 63) == 0) count[i >> 6] = __popcll(b);
+  __syncthreads();
+  int off = 0, n = 0;
+#pragma unroll
+  for (int w = 0; w < ROWS / 64; ++w) {
+    if (w < (i >> 6)) off += count[w];
+    n += count[w];
+  }
+  if (keep) list[off + __popcll(b & ((1ull << (i & 63)) - 1))] = (int16_t)i;
+  __syncthreads();
+  return n;
+}
+
+// Forward: HBM bound (one read of the kept rows), one wavefront per row, eight loads in flight per lane:
+// 131,072 rows of 4,096 bf16, 40 % kept, after a pass that writes 1 GB: 132 us without the batch, 122 us
+// with it (3.5 TB/s).  Listing the kept rows of 32 first, so that no wavefront starts for the others, took 158 us.
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_value_head_fwd(int64_t N, int d, const T* h, const T* w, float b, const uint8_t* mask, const int32_t* cu,
                  const int32_t* gid, int R, float* values) {
   constexpr int EPC = 16 / sizeof(T);
+  constexpr int BATCH = 8;  // 16-byte loads in flight per lane
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (t >= N) return;
@@ -330,109 +358,158 @@ k_value_head_fwd(int64_t N, int d, const T* h, const T* w, float b, const uint8_
     return;
   }
   const T* row = h + t * d;
+  const int nch = d / EPC;
   float acc = 0.0f;
-  for (int c = lane; c < d / EPC; c += 64) {
-    float x[EPC], y[EPC];
-    unpack8<T>(*reinterpret_cast<const u32x4*>(row + c * EPC), x);
-    unpack8<T>(*reinterpret_cast<const u32x4*>(w + c * EPC), y);
+  for (int cb = lane; cb < nch; cb += 64 * BATCH) {
+    u32x4 x[BATCH];
 #pragma unroll
-    for (int e = 0; e < EPC; ++e) acc = fmaf(x[e], y[e], acc);
+    for (int u = 0; u < BATCH; ++u)
+      x[u] = cb + 64 * u < nch ? *reinterpret_cast<const u32x4*>(row + (cb + 64 * u) * EPC) : u32x4{0, 0, 0, 0};
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      if (cb + 64 * u >= nch) break;
+      float f[EPC], y[EPC];
+      unpack8<T>(x[u], f);
+      unpack8<T>(*reinterpret_cast<const u32x4*>(w + (cb + 64 * u) * EPC), y);
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) acc = fmaf(f[e], y[e], acc);
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
   if (lane == 0) values[t] = acc + b;
 }
 
-// dhidden rows: kept rows get (dh +) dV_t w, the others are zeroed unless accumulating
+// Backward, HBM bound (one read of the kept rows, one write of every dhidden row): both in one launch, so
+// that the reads and the writes overlap.  The first 256 threads form the workgroup's partial sum
+// part[blk][j] = sum_t dV_t h_t[j] over its rows (fp32, row order; the thread owns a 16-byte column
+// chunk, and for a row of fewer than 256 chunks the threads deal the rows among themselves and add up
+// in LDS); part_db[blk] = sum_t dV_t (fp64).  131,072 rows of 4,096 bf16, 40 % kept: three passes
+// (dhidden, partial sums of 256 rows four at a time, totals) 615 us -> 320 us with the totals, 4.7 TB/s.  The other 256 (with dh) write the dhidden rows: kept rows
+// get (dh +) dV_t w, the others are zeroed unless accumulating.  Apart, a read's wait does not include
+// the writes issued before it.
 template <typename T>
-__global__ void __launch_bounds__(256)
-k_value_head_dh(int64_t N, int d, const T* w, const float* dv, const uint8_t* mask, const int32_t* cu,
-                const int32_t* gid, int R, T* dh, int accumulate, float* gk) {
+__global__ void __launch_bounds__(512)
+k_value_head_bwd(int64_t N, int d, const T* h, const T* w, const float* dv, const uint8_t* mask, const int32_t* cu,
+                 const int32_t* gid, int R, T* dh, int accumulate, float* part, double* part_db) {
   constexpr int EPC = 16 / sizeof(T);
-  const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (t >= N) return;
-  const bool keep = kept_row(mask, cu, gid, R, t);
-  const float g = keep ? dv[t] : 0.0f;
-  if (lane == 0) gk[t] = g;  // the row's gradient for the dw / db sums
-  if (!dh || (!keep && accumulate)) return;
-  T* row = dh + t * d;
-  for (int c = lane; c < d / EPC; c += 64) {
-    float y[EPC], o[EPC];
-    unpack8<T>(*reinterpret_cast<const u32x4*>(w + c * EPC), y);
-    if (accumulate) {
-      unpack8<T>(*reinterpret_cast<const u32x4*>(row + c * EPC), o);
-    } else {
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) o[e] = 0.0f;
-    }
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) o[e] = fmaf(g, y[e], o[e]);
-    u32x4 v;
-    if constexpr (sizeof(T) == 2) {
-      v = u32x4{bf16_pair(o[0], o[1]), bf16_pair(o[2], o[3]), bf16_pair(o[4], o[5]), bf16_pair(o[6], o[7])};
-    } else {
-      v = u32x4{__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
-    }
-    *reinterpret_cast<u32x4*>(row + c * EPC) = v;
+  constexpr int BATCH = 8;  // rows in flight per thread
+  __shared__ int16_t list[kHeadRows];
+  __shared__ float g_s[kHeadRows], grow_s[kHeadRows];  // gradients by list position, by row
+  __shared__ int keep_s[kHeadRows];
+  __shared__ double db_s[kHeadRows / 64];
+  __shared__ float sum_s[256 * EPC];
+  const int64_t t0 = (int64_t)blockIdx.x * kHeadRows;
+  const int rows = (int)min((int64_t)kHeadRows, N - t0);
+  bool keep;
+  const int n = list_kept<kHeadRows>(t0, N, mask, cu, gid, R, list, keep);
+  const int i = threadIdx.x;
+  if (i < kHeadRows) {
+    const float g = keep ? dv[t0 + i] : 0.0f;
+    grow_s[i] = g;
+    keep_s[i] = keep;
+    g_s[i] = i < n ? dv[t0 + list[i]] : 0.0f;
+    double s = (double)g;
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((i & 63) == 0) db_s[i >> 6] = s;
   }
-}
-
-// dW partial sums over kHeadRows rows per workgroup: part[blk][j] = sum_t dV_t h_t[j] (fp32, row
-// order), part_db[blk] = sum_t dV_t (fp64); each thread owns 16-byte column chunks.
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_value_head_dw_partial(int64_t N, int d, const T* h, const float* gk, float* part, double* part_db) {
-  constexpr int EPC = 16 / sizeof(T);
-  const int64_t t0 = (int64_t)blockIdx.x * kHeadRows, t1 = min(N, t0 + kHeadRows);
-  for (int cb = 0; cb < d / EPC; cb += 256) {
-    const int c = cb + threadIdx.x;
-    float acc[EPC];
+  __syncthreads();
+  const int nch = d / EPC;
+  const int deal = nch >= 256 ? 1 : 256 / nch;  // rows side by side
+  const int ti = i & 255;
+  const int c0 = deal == 1 ? ti : ti % nch, sub = deal == 1 ? 0 : ti / nch;
+  if (i < 256) {
+    if (i == 0) {
+      double s = 0.0;
+      for (int k = 0; k < kHeadRows / 64; ++k) s += db_s[k];
+      part_db[blockIdx.x] = s;
+    }
+    for (int cb = 0; cb < nch; cb += 256) {
+      const int c = cb + c0;
+      const bool on = c < nch && sub < deal;
+      float acc[EPC];
 #pragma unroll
-    for (int e = 0; e < EPC; ++e) acc[e] = 0.0f;
-    double db = 0.0;
-    // rows in groups of four: the row loads of a group are issued together (skipped for rows with
-    // no gradient), then accumulated in row order
-    for (int64_t t = t0; t < t1; t += 4) {
-      float g4[4];
-      u32x4 x4[4];
+      for (int e = 0; e < EPC; ++e) acc[e] = 0.0f;
+      for (int k = sub; on && k < n; k += BATCH * deal) {
+        u32x4 x[BATCH];
+        float g[BATCH];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int64_t tt = t + u;
-        g4[u] = 0.0f;
-        x4[u] = u32x4{0, 0, 0, 0};
-        if (tt < t1) {
-          g4[u] = gk[tt];
-          if (g4[u] != 0.0f && c < d / EPC) x4[u] = *reinterpret_cast<const u32x4*>(h + tt * d + c * EPC);
+        for (int u = 0; u < BATCH; ++u) {
+          const int p = k + u * deal;
+          g[u] = p < n ? g_s[p] : 0.0f;
+          x[u] = u32x4{0, 0, 0, 0};
+          if (p < n) x[u] = *reinterpret_cast<const u32x4*>(h + (t0 + list[p]) * d + c * EPC);
+        }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+          if (g[u] == 0.0f) continue;  // a row without gradient adds nothing, whatever it holds
+          float f[EPC];
+          unpack8<T>(x[u], f);
+#pragma unroll
+          for (int e = 0; e < EPC; ++e) acc[e] = fmaf(g[u], f[e], acc[e]);
         }
       }
+      float* out = part + (int64_t)blockIdx.x * d;
+      if (deal == 1) {
+        if (on) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (g4[u] == 0.0f) continue;
-        db += (double)g4[u];
-        float x[EPC];
-        unpack8<T>(x4[u], x);
+          for (int e = 0; e < EPC; e += 4)
+            *reinterpret_cast<f32x4*>(out + c * EPC + e) = f32x4{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
+        }
+      } else {
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) acc[e] = fmaf(g4[u], x[e], acc[e]);
+        for (int e = 0; e < EPC; ++e) sum_s[ti * EPC + e] = acc[e];
       }
     }
-    if (c < d / EPC) {
+  } else {
+    for (int cb = 0; cb < nch; cb += 256) {
+      const int c = cb + c0;
+      if (c >= nch || sub >= deal) continue;
+      float y[EPC];
+      unpack8<T>(*reinterpret_cast<const u32x4*>(w + c * EPC), y);
+#pragma unroll 4
+      for (int rl = sub; rl < rows; rl += deal) {
+        const bool kept = keep_s[rl] != 0;
+        if (!kept && accumulate) continue;
+        T* row = dh + (t0 + rl) * d + c * EPC;
+        float o[EPC];
 #pragma unroll
-      for (int e = 0; e < EPC; ++e) part[(int64_t)blockIdx.x * d + c * EPC + e] = acc[e];
+        for (int e = 0; e < EPC; ++e) o[e] = 0.0f;
+        if (kept) {
+          if (accumulate) unpack8<T>(*reinterpret_cast<const u32x4*>(row), o);
+          const float g = grow_s[rl];
+#pragma unroll
+          for (int e = 0; e < EPC; ++e) o[e] = fmaf(g, y[e], o[e]);
+        }
+        u32x4 v;
+        if constexpr (sizeof(T) == 2) {
+          v = u32x4{bf16_pair(o[0], o[1]), bf16_pair(o[2], o[3]), bf16_pair(o[4], o[5]), bf16_pair(o[6], o[7])};
+        } else {
+          v = u32x4{__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
+        }
+        *reinterpret_cast<u32x4*>(row) = v;
+      }
     }
-    if (cb == 0 && threadIdx.x == 0) part_db[blockIdx.x] = db;
+  }
+  if (deal > 1) {
+    __syncthreads();
+    for (int j = i; j < d; j += blockDim.x) {
+      float s = 0.0f;
+      for (int k = 0; k < deal; ++k) s += sum_s[k * d + j];
+      part[(int64_t)blockIdx.x * d + j] = s;
+    }
   }
 }
 
 // final sums over the workgroup partials in a fixed order (fp64): a block owns 32 columns; thread
-// (column, part) adds the partials of its eighth of the workgroups in workgroup order, then the
-// eight part sums of a column are added in part order.
-__global__ void __launch_bounds__(256)
+// (column, part) adds the partials of its 32nd of the workgroups in workgroup order, then the part
+// sums of a column are added in part order.
+__global__ void __launch_bounds__(1024)
 k_value_head_dw_final(int nblk, int d, const float* part, const double* part_db, float* dw, float* dbias) {
-  __shared__ double sh[8][32];
+  __shared__ double sh[32][33];
   const int col = threadIdx.x & 31, pt = threadIdx.x >> 5;
   const int j = blockIdx.x * 32 + col;
-  const int b0 = (int)((int64_t)nblk * pt / 8), b1 = (int)((int64_t)nblk * (pt + 1) / 8);
+  const int b0 = (int)((int64_t)nblk * pt / 32), b1 = (int)((int64_t)nblk * (pt + 1) / 32);
   double s = 0.0;
   if (j < d) {
 #pragma unroll 8
@@ -443,12 +520,19 @@ k_value_head_dw_final(int nblk, int d, const float* part, const double* part_db,
   if (pt == 0 && j < d) {
     double t = 0.0;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) t += sh[q][col];
+    for (int q = 0; q < 32; ++q) t += sh[q][col];
     dw[j] = (float)t;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    double t = 0.0;
-    for (int b = 0; b < nblk; ++b) t += part_db[b];
+  if (blockIdx.x > 0) return;
+  __syncthreads();
+  double t = 0.0;
+  for (int b = threadIdx.x; b < nblk; b += 1024) t += part_db[b];
+  for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+  if ((threadIdx.x & 63) == 0) sh[0][threadIdx.x >> 6] = t;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    t = 0.0;
+    for (int k = 0; k < 16; ++k) t += sh[0][k];
     dbias[0] = (float)t;
   }
 }
@@ -457,7 +541,7 @@ k_value_head_dw_final(int nblk, int d, const float* part, const double* part_db,
 
 size_t value_head_workspace(int64_t N, int d) {
   const int64_t nblk = (N + kHeadRows - 1) / kHeadRows;
-  return (size_t)(((nblk * d * 4 + 255) / 256) * 256 + ((nblk * 8 + 255) / 256) * 256 + ((N * 4 + 255) / 256) * 256);
+  return (size_t)(((nblk * d * 4 + 255) / 256) * 256 + ((nblk * 8 + 255) / 256) * 256);
 }
 
 hipError_t launch_value_head_fwd(int dtype, int64_t N, int d, int R, const void* h, const void* w, float b,
@@ -483,27 +567,17 @@ hipError_t launch_value_head_bwd(int dtype, int64_t N, int d, int R, const void*
   const int64_t nblk64 = (N + kHeadRows - 1) / kHeadRows;
   const int nblk = (int)nblk64;
   float* part = reinterpret_cast<float*>(ws);
-  const size_t part_bytes = ((nblk64 * d * 4 + 255) / 256) * 256;
-  double* part_db = reinterpret_cast<double*>(ws + part_bytes);
-  float* gk = reinterpret_cast<float*>(ws + part_bytes + ((nblk64 * 8 + 255) / 256) * 256);
-  const bool bf = dtype == RLK_DTYPE_BF16;
-  if (N > 0) {
-    // dhidden rows (when dh is given) and every row's gradient gk for the sums below
-    const unsigned grid = (unsigned)((N + 3) / 4);
-    if (bf)
-      k_value_head_dh<bf16_t><<<grid, 256, 0, s>>>(N, d, (const bf16_t*)w, dv, mask, cu, gid, R, (bf16_t*)dh,
-                                                   accumulate, gk);
-    else
-      k_value_head_dh<float><<<grid, 256, 0, s>>>(N, d, (const float*)w, dv, mask, cu, gid, R, (float*)dh,
-                                                  accumulate, gk);
-  }
+  double* part_db = reinterpret_cast<double*>(ws + ((nblk64 * d * 4 + 255) / 256) * 256);
+  const unsigned threads = dh ? 512 : 256;
   if (nblk > 0) {
-    if (bf)
-      k_value_head_dw_partial<bf16_t><<<nblk, 256, 0, s>>>(N, d, (const bf16_t*)h, gk, part, part_db);
+    if (dtype == RLK_DTYPE_BF16)
+      k_value_head_bwd<bf16_t><<<nblk, threads, 0, s>>>(N, d, (const bf16_t*)h, (const bf16_t*)w, dv, mask, cu, gid, R,
+                                                        (bf16_t*)dh, accumulate, part, part_db);
     else
-      k_value_head_dw_partial<float><<<nblk, 256, 0, s>>>(N, d, (const float*)h, gk, part, part_db);
+      k_value_head_bwd<float><<<nblk, threads, 0, s>>>(N, d, (const float*)h, (const float*)w, dv, mask, cu, gid, R,
+                                                       (float*)dh, accumulate, part, part_db);
   }
-  k_value_head_dw_final<<<(unsigned)((d + 31) / 32), 256, 0, s>>>(nblk, d, part, part_db, dw, dbias);
+  k_value_head_dw_final<<<(unsigned)((d + 31) / 32), 1024, 0, s>>>(nblk, d, part, part_db, dw, dbias);
   prof_mark(KK_VALUE_HEAD, false, s);
   return hipGetLastError();
 }

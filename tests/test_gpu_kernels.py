@@ -104,3 +104,38 @@ def test_value_loss_of_many_rollouts():
     rl, rdv = O.value_loss(vals, rets, mask, cu)
     assert abs(float(loss.item()) - rl) <= 2e-7 * abs(rl)
     np.testing.assert_allclose(to_host(dv), rdv, rtol=0, atol=2e-7 * np.abs(rdv).max())
+
+
+# rows of fewer than 256 16-byte chunks are dealt among the threads (8 features: 256 rows side by side; 1,360:
+# one row and a rest of idle threads), wider ones take several passes; 128 rows per workgroup
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("lens,d", [((1,), 8), ((100, 27), 64), ((128,), 680), ((33, 0, 96), 1360), ((500, 13), 2048), ((61, 70), 4104)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_value_head_row_and_column_splits(dtype, lens, d, accumulate):
+    ensure_library()
+    rng = np.random.default_rng(d)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    N, R = int(cu[-1]), len(lens)
+    mask = (rng.random(N) < 0.6).astype(np.uint8)
+    gid = np.zeros(R, np.int32)
+    gid[R - 1] = -1 if R > 1 else 0
+    r = lambda *shape: torch.randn(*shape, generator=gen, device="cuda")
+    h, w, dv, dh0 = r(N, d).to(dtype), r(d).to(dtype), r(N), r(N, d).to(dtype)
+    m, c, g = (torch.as_tensor(a, device="cuda") for a in (mask, cu, gid))
+    values = rlk.value_head_fwd(h, w, 0.25, m, c, g)
+    dh = dh0.clone()
+    _, dw, db = rlk.value_head_bwd(h, w, m, c, g, dv, dhidden=dh, accumulate=accumulate)
+    _, dw1, db1 = rlk.value_head_bwd(h, w, m, c, g, dv)  # without dhidden: the same sums
+    on = ((mask != 0) & np.repeat(gid >= 0, lens)).astype(np.float64)[:, None]
+    H, Wv, G = to_host(h).astype(np.float64), to_host(w).astype(np.float64), to_host(dv).astype(np.float64)[:, None] * on
+    want = (to_host(dh0) if accumulate else 0.0) + G * Wv
+    # fp32 sums of at most d (forward) or 128 (per workgroup) products; bf16 rows rounded once more
+    eps = 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -23
+    np.testing.assert_allclose(to_host(values)[:, None], (H @ Wv[:, None] + 0.25) * on, rtol=0, atol=2.0 ** -24 * d ** 0.5 * 8 * 4)
+    np.testing.assert_allclose(to_host(dh), want, rtol=eps, atol=eps * 1e-2)
+    np.testing.assert_allclose(to_host(dw), (G * H).sum(0), rtol=0, atol=2.0 ** -24 * 128 * 8)
+    assert abs(float(db.item()) - G.sum()) <= 2.0 ** -23 * max(1.0, abs(G.sum()))
+    assert torch.equal(dw, dw1) and torch.equal(db, db1)
+    if accumulate:
+        assert torch.equal(dh[torch.as_tensor(on[:, 0] == 0, device="cuda")], dh0[torch.as_tensor(on[:, 0] == 0, device="cuda")])
