@@ -2,10 +2,13 @@
 // epilogues.  One core computes C[m][n] = sum_k A[m][k] * B[n][k] with both operands
 // K-contiguous ("NT"); the three uses are
 //   forward : A = W [V, d],          B = gathered hidden [tokens, d]   -> online log-softmax
-//   dhidden : A = dz [tokens, Vp],   B = W^T [d, Vp]                   -> scatter to dh[idx]
+//   dhidden : A = dz [tokens, Vp],   B = W^T [d, Vp] (or W [V, d])     -> scatter to dh[idx]
 //   dW      : A = dz^T [Vp, tokens], B = hidden^T [d, tokens]          -> fp32 dW (+)=
 // In the token-reference layout (dz = diag(s) q) the gradient GEMMs read the forward's q and q^T
 // as A, the dhidden epilogue scales its rows by s and the dW GEMM's B is (diag(s) hidden)^T.
+//
+// For few tokens the bf16 dhidden GEMM reads W as it lies ("K-major": K rows of features) by transposing
+// fragment reads, which saves the W^T copy.
 //
 // Tile geometry (gfx950): a 256 x 256 output tile per workgroup of 2 x 4 wavefronts, two per SIMD.
 // The tile is four 128 x 128 quadrants; in each, wavefront (wm, wn) owns the 64 x 32 block at
@@ -43,6 +46,7 @@ constexpr int WTM = HALF / WAVES_M;     // rows of a wavefront's block in a quad
 constexpr int WTN = HALF / WAVES_N;     // columns of it
 constexpr int MB = WTM / 16, NB = WTN / 16;  // 16x16 MFMA blocks of it
 constexpr int KS = kGemmSliceBytes;     // bytes of K per pipeline slice per row
+constexpr int KSE = KS / 2;             // K elements of it (bf16)
 constexpr int CPR = KS / 16;            // 16-byte chunks per row of a slice
 constexpr int RPI = 64 / CPR;           // rows per LDS-DMA instruction
 constexpr int IPH = HALF / RPI / NWAVE; // LDS-DMA instructions per wavefront per half tile
@@ -70,6 +74,10 @@ constexpr int kBufferFlags = 0x00020000;  // raw buffer: 32-bit data format, off
 // immediate offsets, and a copy's lane offset depends on its instruction only through the
 // instruction's parity.
 __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
+// The same for a K-major half tile, rows of 256 bytes: in a transposing read the 16 lanes of a group take
+// 32 bytes of each of four K rows 8 lg .. + 3, and the 32-byte unit's XOR with kswz(row) spreads the
+// 16 rows of a wavefront's read over the 8 units of the 256-byte bank window, two to each.
+__device__ __forceinline__ int kswz(int r) { return (r & 3) | ((r >> 3) & 1) << 2; }
 
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding: vmcnt[3:0] in
 // bits 3:0, vmcnt[5:4] in bits 15:14, expcnt 7 and lgkmcnt 15 = no wait).
@@ -160,6 +168,39 @@ __device__ __forceinline__ bool map_tile(int tm, int tn, int& tile_m, int& tile_
   return true;
 }
 
+// The memory step of a K-major operand: fragments f[i][kk] of its 16-row blocks by transposing reads
+// (block i's two K steps at LDS address u[i] + AT), the two copies of one of its half tiles (range rs,
+// vector offsets o, scalar offsets so, LDS destinations dst), and the step's waits.  One statement: the
+// compiler would wait for every copy in flight before each transposing read of its own (it takes the
+// read to alias the copies' LDS writes).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"  // m0 is set before each copy, here and by the compiler
+template <int AT, int VM>
+__device__ __forceinline__ void kmajor_step(const int (&u)[NB], u32x4 (&f)[NB][2], u32x4 rs, const uint32_t (&o)[2],
+                                            uint32_t so0, uint32_t so1, int dst0, int dst1) {
+  static_assert(AT + 36 * 256 < 65536, "offset field");
+  static_assert(NB == 2, "operand list");
+  u32x2 l[NB][2], h[NB][2];
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8 offset:%10\n\tds_read_b64_tr_b16 %1, %8 offset:%11\n\t"
+      "ds_read_b64_tr_b16 %2, %9 offset:%10\n\tds_read_b64_tr_b16 %3, %9 offset:%11\n\t"
+      "ds_read_b64_tr_b16 %4, %8 offset:%12\n\tds_read_b64_tr_b16 %5, %8 offset:%13\n\t"
+      "ds_read_b64_tr_b16 %6, %9 offset:%12\n\tds_read_b64_tr_b16 %7, %9 offset:%13\n\t"
+      "s_mov_b32 m0, %19\n\ts_nop 0\n\tbuffer_load_dwordx4 %15, %14, %17 offen lds\n\t"
+      "s_mov_b32 m0, %20\n\ts_nop 0\n\tbuffer_load_dwordx4 %16, %14, %18 offen lds\n\t"
+      "s_waitcnt vmcnt(%21) lgkmcnt(0)"
+      : "=&v"(l[0][0]), "=&v"(h[0][0]), "=&v"(l[1][0]), "=&v"(h[1][0]), "=&v"(l[0][1]), "=&v"(h[0][1]),
+        "=&v"(l[1][1]), "=&v"(h[1][1])
+      : "v"(u[0]), "v"(u[1]), "i"(AT), "i"(AT + 4 * 256), "i"(AT + 32 * 256), "i"(AT + 36 * 256), "s"(rs), "v"(o[0]),
+        "v"(o[1]), "s"(so0), "s"(so1), "s"(dst0), "s"(dst1), "i"(VM)
+      : "memory", "m0");
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) f[i][kk] = u32x4{l[i][kk].x, l[i][kk].y, h[i][kk].x, h[i][kk].y};
+}
+#pragma clang diagnostic pop
+
 // Reference of the stored probabilities of chunk column n in a forward tile with maximum m: m itself,
 // or with a.zr (token-reference layout) the column's reference logit r, clamped to m - kRefSpan where
 // it lies further below (then, with mark, the chunk is flagged: its dz needs the explicit pass).
@@ -172,7 +213,8 @@ __device__ __forceinline__ float tile_ref(const GemmArgs& a, float m, int n, int
   return m - kRefSpan;
 }
 
-template <typename T, int EPI, bool STORE_Q, bool KTAIL>
+// KM_B (dhidden): B is [K][N], K-major.
+template <typename T, int EPI, bool STORE_Q, bool KTAIL, bool KM_B = false>
 __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[EPI == EPI_FWD ? LDS_B : PIPE_B];
 
@@ -201,8 +243,11 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
   const uint32_t lda_b = (uint32_t)(a.lda * (int64_t)sizeof(T)), ldb_b = (uint32_t)(a.ldb * (int64_t)sizeof(T));
   const int rows_a = min(kTile, M - tile_m * kTile), rows_b = min(kTile, N - tile_n * kTile);
   char* const pa = const_cast<char*>(reinterpret_cast<const char*>(a.A) + (int64_t)tile_m * kTile * lda_b);
-  char* const pb = const_cast<char*>(reinterpret_cast<const char*>(a.B) + (int64_t)tile_n * kTile * ldb_b);
-  const uint32_t size_a = (uint32_t)rows_a * lda_b, size_b = (uint32_t)rows_b * ldb_b;
+  char* const pb = const_cast<char*>(reinterpret_cast<const char*>(a.B) +
+                                     (int64_t)tile_n * kTile * (KM_B ? (int64_t)sizeof(T) : (int64_t)ldb_b));
+  // bytes of the whole panel, or (K-major) of one of its K rows
+  const uint32_t size_a = (uint32_t)rows_a * lda_b;
+  const uint32_t size_b = KM_B ? (uint32_t)rows_b * (uint32_t)sizeof(T) : (uint32_t)rows_b * ldb_b;
   const int64_t Kb = (int64_t)K * sizeof(T);
   int nk = (int)((Kb + KS - 1) / KS);
   // split K: this workgroup covers slices [ks0, ks0 + nk) of the tile's K range
@@ -220,6 +265,9 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
   // Rows past the panel (ragged last tiles) read as zero because their vector offset alone is out of
   // range: 0x80000000 >= num_records (every 256-row panel is at most 2 GiB, checked by the host), so
   // the read stays inside the panel whether or not the hardware adds the scalar offset to the check.
+  //   A K-major half tile is KSE K rows of 128 elements (256 bytes): an instruction moves four rows, lane
+  // l the 16-byte chunk (l % 16) ^ 2 kswz(row) of row l / 16.  Chunks past the operand's last column are
+  // put out of range in the same way, K rows past the last one by the size of the slice's range.
   uint32_t vo_a[2][IPH], vo_b[2][IPH];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
@@ -228,16 +276,34 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
       const int row = (wid * IPH + j) * RPI + lane / CPR;
       const int chunk = (lane % CPR) ^ swz(row);
       vo_a[h][j] = h * HALF + row < rows_a ? (uint32_t)(lane / CPR) * lda_b + chunk * 16 : 0x80000000u;
-      vo_b[h][j] = h * HALF + row < rows_b ? (uint32_t)(lane / CPR) * ldb_b + chunk * 16 : 0x80000000u;
+      if constexpr (KM_B) {
+        const uint32_t col = h * 2 * HALF + ((lane & 15) ^ (2 * kswz((wid * IPH + j) * 4 + lane / 16))) * 16;
+        vo_b[h][j] = col < size_b ? (uint32_t)(lane / 16) * ldb_b + col : 0x80000000u;
+      } else {
+        vo_b[h][j] = h * HALF + row < rows_b ? (uint32_t)(lane / CPR) * ldb_b + chunk * 16 : 0x80000000u;
+      }
     }
+  // Range of slice kt of a K-major B: its K rows of [0, a.V) in this split
+  auto kmajor_range = [&](int kt) {
+    const int left = min(a.V, (ks0 + nk) * KSE) - (kt + ks0) * KSE;
+    const uint64_t base = reinterpret_cast<uint64_t>(pb) + (uint64_t)(kt + ks0) * (KSE * (uint64_t)ldb_b);
+    return u32x4{(uint32_t)base, (uint32_t)(base >> 32) & 0xffffu,
+                 left > 0 ? (uint32_t)(min(left, KSE) - 1) * ldb_b + size_b : 0u, (uint32_t)kBufferFlags};
+  };
   // this wavefront's copies of half h of one operand of slice kt into buffer kt % 2.  Slices past the
   // last one are copied from an empty panel (zeros, no memory access), which keeps the number of
   // copies in flight the same to the end of the loop.
   auto copy_half = [&](bool op_b, int h, int kt, int buf) {
     const uint32_t kb = (uint32_t)(kt + ks0) * KS;
-    const uint32_t size = kt < nk ? (op_b ? size_b : size_a) : 0u;
-    const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(op_b ? pb : pa, (short)0, (int)size, kBufferFlags);
+    const bool km = KM_B && op_b;
+    char* base = op_b ? pb : pa;
+    uint32_t size = kt < nk ? (op_b ? size_b : size_a) : 0u;
+    if (km) {
+      const u32x4 r = kmajor_range(kt);
+      base = reinterpret_cast<char*>((uint64_t)r.x | (uint64_t)r.y << 32);
+      size = r.z;
+    }
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, (short)0, (int)size, kBufferFlags);
 #pragma unroll
     for (int j = 0; j < IPH; ++j) {
       uint32_t o = op_b ? vo_b[h][j] : vo_a[h][j];
@@ -249,12 +315,23 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
       }
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rs, LDSP(smem + (op_b ? OPND_B : 0) + (buf * 2 + h) * HALF_B + (wid * IPH + j) * 1024), 16, o,
-          kb + (uint32_t)(h * HALF + (wid * IPH + j) * RPI) * (op_b ? ldb_b : lda_b), 0, 0);
+          km ? (uint32_t)((wid * IPH + j) * 4) * ldb_b
+             : kb + (uint32_t)(h * HALF + (wid * IPH + j) * RPI) * (op_b ? ldb_b : lda_b), 0, 0);
     }
   };
   // Fragment reads: lane (lr, lg) takes logical K chunk 4 kk + lg of row lr of each 16-row block.
+  // K-major: the same eight K elements of the same row by two transposing reads; in one, the 16 lanes of
+  // group lg address K rows 32 kk + 8 lg + 4 hf + lr / 4, 8 bytes each of the block's 32, and lane lr
+  // receives column lr of those four rows.
   const int rd_a = (wm * WTM + lr) * KS, rd_b = OPND_B + (wn * WTN + lr) * KS;
   const int ch0 = (lg ^ swz(lr)) * 16, ch1 = ((4 + lg) ^ swz(lr)) * 16;
+  int ku_b[NB];
+  {
+    const int krow = 8 * lg + (lr >> 2);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+      ku_b[nb] = (int)(uintptr_t)LDSP(smem) + OPND_B + krow * 256 + (lr & 3) * 8 + ((wn * NB + nb) ^ kswz(krow)) * 32;
+  }
   u32x4 fa[MB][2], fb[2][NB][2];
   auto read_a = [&](int buf, int h) {
 #pragma unroll
@@ -308,19 +385,38 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
   // 155 ms, dW 177 -> 153 ms.  Issuing the copies before the fragment reads costs 5-10 %; raising the
   // copies' lead to six phases, or leaving out s_setprio, changes nothing.
   constexpr int IN_FLIGHT = 5 * IPH;
+  // memory step of a phase that reads half RH of B from buffer RB and copies half CH of slice kt of B into
+  // buffer CB
+  auto step_b = [&](auto RB, auto RH, auto CB, auto CH, int kt) {
+    constexpr int rb = decltype(RB)::value, h = decltype(RH)::value, cb = decltype(CB)::value, ch = decltype(CH)::value;
+    if constexpr (KM_B) {
+      const int dst = (int)(uintptr_t)LDSP(smem) + OPND_B + (cb * 2 + ch) * HALF_B + wid * IPH * 1024;
+      const uint32_t so = (uint32_t)(wid * IPH * 4) * ldb_b;
+      kmajor_step<(rb * 2 + h) * HALF_B, IN_FLIGHT>(ku_b, fb[h], kmajor_range(kt), vo_b[ch], so, so + 4 * ldb_b, dst,
+                                                    dst + 1024);
+    } else {
+      read_b(rb, h);
+      copy_half(true, ch, kt, cb);
+      wait_vmcnt<IN_FLIGHT>();
+    }
+  };
+  const std::integral_constant<int, 0> c0{};
+  const std::integral_constant<int, 1> c1{};
   copy_half(true, 0, 0, 0);
   copy_half(false, 0, 0, 0);
   copy_half(true, 1, 0, 0);
   copy_half(false, 1, 0, 0);
   copy_half(true, 0, 1, 1);
   copy_half(false, 0, 1, 1);
-  copy_half(true, 1, 1, 1);
   wait_vmcnt<IN_FLIGHT>();
   block_barrier();
-  read_b(0, 0);
+  step_b(c0, c0, c1, c1, 1);
+  block_barrier();
   if (wm == 1) block_barrier();
   auto slice = [&](int kt, auto BUF) {
     constexpr int buf = decltype(BUF)::value;
+    const std::integral_constant<int, buf> cur{};
+    const std::integral_constant<int, buf ^ 1> nxt{};
     read_a(buf, 0);
     copy_half(false, 1, kt + 1, buf ^ 1);
     wait_vmcnt<IN_FLIGHT>();
@@ -328,9 +424,7 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
     wait_lgkm0();
     mma(0, 0);
     block_barrier();
-    read_b(buf, 1);
-    copy_half(true, 0, kt + 2, buf);
-    wait_vmcnt<IN_FLIGHT>();
+    step_b(cur, c1, cur, c0, kt + 2);
     block_barrier();
     wait_lgkm0();
     mma(0, 1);
@@ -342,17 +436,15 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
     wait_lgkm0();
     mma(1, 0);
     block_barrier();
-    read_b(buf ^ 1, 0);
-    copy_half(true, 1, kt + 2, buf);
-    wait_vmcnt<IN_FLIGHT>();
+    step_b(nxt, c0, cur, c1, kt + 2);
     block_barrier();
     wait_lgkm0();
     mma(1, 1);
     block_barrier();
   };
   for (int kt = 0; kt < nk; kt += 2) {
-    slice(kt, std::integral_constant<int, 0>{});
-    if (kt + 1 < nk) slice(kt + 1, std::integral_constant<int, 1>{});
+    slice(kt, c0);
+    if (kt + 1 < nk) slice(kt + 1, c1);
   }
   if (wm == 0) block_barrier();
   // the epilogues reuse the LDS of the pipeline
@@ -653,7 +745,12 @@ inline unsigned tiles(int64_t n) { return (unsigned)((n + kTile - 1) / kTile); }
 template <typename T, int EPI>
 hipError_t grad_impl(const GemmArgs& a, unsigned ntiles, hipStream_t s) {
   const unsigned ny = a.ksplit > 1 ? (unsigned)a.ksplit : 1u;
-  k_gemm<T, EPI, false, false><<<dim3(ntiles, ny), NT, 0, s>>>(a);
+  if constexpr (EPI == EPI_DH && sizeof(T) == 2) {
+    if (a.b_kmajor) k_gemm<T, EPI, false, false, true><<<dim3(ntiles, ny), NT, 0, s>>>(a);
+    else k_gemm<T, EPI, false, false><<<dim3(ntiles, ny), NT, 0, s>>>(a);
+  } else {
+    k_gemm<T, EPI, false, false><<<dim3(ntiles, ny), NT, 0, s>>>(a);
+  }
   if (a.ksplit > 1) {
     const int64_t total = (int64_t)a.M * a.N;
     const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 8192);

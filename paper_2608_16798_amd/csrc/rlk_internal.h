@@ -124,7 +124,8 @@ struct WsLayout {
   size_t ht = 0;                   // T [d][Mc]
   size_t q = 0;                    // T [Mc][ldq]
   size_t dzt = 0;                  // T [Vp][ldt]
-  size_t wt = 0;                   // T [d][ldw]
+  size_t wt = 0;                   // T [d][ldw]; not there with w_kmajor
+  bool w_kmajor = false;           // the dhidden GEMM reads W as it lies
   size_t zr = 0, st = 0;           // float [Mc]: reference logit and dz row scale per chunk row
   size_t part = 0;                 // float split-K partials of the dhidden / dW GEMMs (0 = none)
   SplitK sk_dh = {1, 1}, sk_dw = {1, 1};
@@ -276,7 +277,7 @@ struct GemmArgs {
   float *pm, *ps, *pu;   // [nvt][Mc]
   void* q;               // [Mc][ldq]
   int64_t ldq;
-  int V;
+  int V;                 // forward; K-major B: its K rows
   float inv_tau;         // logits z = acc / tau
   // token-reference layout (bf16 forward; zr = NULL: each tile stores against its own maximum):
   // reference logits zr [Mc], q^T [Vp][ldqt] written beside q, *fb = 1 where a tile clamps
@@ -284,6 +285,8 @@ struct GemmArgs {
   void* qt;
   int64_t ldqt;
   int32_t* fb;
+  // dhidden (bf16): B is W [V][ldb], K-major, instead of W^T
+  int b_kmajor;
   // dhidden epilogue
   void* out;
   const int32_t* idx;

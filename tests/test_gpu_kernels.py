@@ -27,10 +27,11 @@ def _all_policy(dtype, tokens, d, V):
 
 
 # K slices of the forward: 1, 2, 3 (whole and with a tail); token and vocabulary tiles one short of, at and
-# one past the tile's and its halves' edges
+# one past the tile's and its halves' edges; bf16 calls of more than 8,192 rows read W^T in the dhidden GEMM, the
+# others W itself
 @pytest.mark.parametrize("dtype,tokens,d,V", [
     ("bf16", 2, 8, 1), ("bf16", 127, 64, 129), ("bf16", 129, 72, 255), ("bf16", 255, 128, 256), ("bf16", 256, 136, 257),
-    ("bf16", 257, 192, 513), ("f32", 127, 8, 129), ("f32", 129, 32, 257), ("f32", 257, 40, 255), ("f32", 255, 96, 300)])
+    ("bf16", 257, 192, 513), ("bf16", 300, 520, 1), ("bf16", 8192, 136, 321), ("bf16", 8193, 136, 321), ("f32", 127, 8, 129), ("f32", 129, 32, 257), ("f32", 257, 40, 255), ("f32", 255, 96, 300)])
 @pytest.mark.parametrize("entropy", [0.0, 1e-2])
 def test_gemm_tile_edges(dtype, tokens, d, V, entropy):
     ensure_library()
