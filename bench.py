@@ -354,10 +354,11 @@ def stats_summary(stats_csv, title, cmd):
     import re
 
     def short(n):
-        m = re.search(r"k_gemm<(?:rlk::)?(\w+), (\d), (\w+), (\w+)>", n)
+        m = re.search(r"k_gemm<(?:rlk::)?(\w+), (\d), (\w+), (\w+)(?:, (\w+))?>", n)
         if m:
             kind = ["fwd_lse", "dh", "dw"][int(m.group(2))]
-            return f"k_gemm<{m.group(1)},{kind},store_q={m.group(3)},ktail={m.group(4)}>"
+            return (f"k_gemm<{m.group(1)},{kind},store_q={m.group(3)},ktail={m.group(4)}"
+                    + (",w_kmajor>" if m.group(5) == "true" else ">"))
         m = re.search(r"rlk::\(anonymous namespace\)::(k_\w+)(<[^>(]*>)?", n)
         return (m.group(1) + (m.group(2) or "")) if m else None
 

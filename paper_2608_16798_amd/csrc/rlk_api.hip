@@ -297,7 +297,7 @@ rlk_status_t layout(const rlk_batch_t* b, bool bwd, int64_t chunk_rows, int64_t 
     L.ht = a.take((size_t)(d * L.ldt * esz));
     L.q = a.take((size_t)(Mc * L.ldq * esz));
     L.dzt = a.take((size_t)(L.Vp * L.ldt * esz));
-    if (!L.w_kmajor) L.wt = a.take((size_t)(d * L.ldw * esz));
+    L.wt = a.take((size_t)(d * L.ldw * esz));  // reserved for every row count
     L.zr = a.take((size_t)Mc * 4);
     L.st = a.take((size_t)Mc * 4);
     // split-K partials of the dhidden and dW GEMMs (used one after the other)

@@ -124,7 +124,7 @@ struct WsLayout {
   size_t ht = 0;                   // T [d][Mc]
   size_t q = 0;                    // T [Mc][ldq]
   size_t dzt = 0;                  // T [Vp][ldt]
-  size_t wt = 0;                   // T [d][ldw]; not there with w_kmajor
+  size_t wt = 0;                   // T [d][ldw]; unused with w_kmajor
   bool w_kmajor = false;           // the dhidden GEMM reads W as it lies
   size_t zr = 0, st = 0;           // float [Mc]: reference logit and dz row scale per chunk row
   size_t part = 0;                 // float split-K partials of the dhidden / dW GEMMs (0 = none)
