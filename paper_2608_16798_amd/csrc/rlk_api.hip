@@ -276,9 +276,8 @@ rlk_status_t layout(const rlk_batch_t* b, bool bwd, int64_t chunk_rows, int64_t 
   L.gstart = a.take((size_t)(R + 1) * 4);
   L.gidx = a.take((size_t)R * 4);
   L.gsize = a.take((size_t)R * 4);
-  L.gmu = a.take((size_t)R * 8);
-  L.gsig = a.take((size_t)R * 8);
-  L.geq = a.take((size_t)R * 4);
+  L.sort_a = a.take((size_t)R * 8);
+  L.sort_b = a.take((size_t)R * 8);
   L.adv = a.take((size_t)R * 4);
   L.rsum = a.take((size_t)R * 8 * kRollSums);
   L.pm = a.take((size_t)L.nvt * Mc * 4);
@@ -332,9 +331,9 @@ constexpr size_t advantage_ws_bytes(int32_t R) {
   a.take((size_t)(R + 1) * 4);  // run starts
   a.take((size_t)R * 4);  // gidx
   a.take((size_t)R * 4);  // gsize
-  a.take((size_t)R * 8);  // mu
-  a.take((size_t)R * 8);  // sigma
-  a.take((size_t)R * 4);  // all-equal flags
+  a.take((size_t)R * 8);  // sort scratch
+  a.take((size_t)R * 8);  // sort scratch
+  a.take((size_t)R * 4);  // unused (the size is part of the interface)
   return a.off;
 }
 
@@ -444,15 +443,12 @@ rlk_status_t advantage_call(int32_t R, const float* rewards, const int32_t* grou
   int32_t* gstart = reinterpret_cast<int32_t*>(w + a.take((size_t)(R + 1) * 4));
   int32_t* gidx_ws = reinterpret_cast<int32_t*>(w + a.take((size_t)R * 4));
   int32_t* gsize = reinterpret_cast<int32_t*>(w + a.take((size_t)R * 4));
-  double* gmu = reinterpret_cast<double*>(w + a.take((size_t)R * 8));
-  double* gsig = reinterpret_cast<double*>(w + a.take((size_t)R * 8));
-  int32_t* geq = reinterpret_cast<int32_t*>(w + a.take((size_t)R * 4));
+  double* sort_a = reinterpret_cast<double*>(w + a.take((size_t)R * 8));
+  double* sort_b = reinterpret_cast<double*>(w + a.take((size_t)R * 8));
   int32_t* gidx = group_index ? group_index : gidx_ws;
-  RLK_TRY(launch_begin(reinterpret_cast<int32_t*>(hdr), nullptr, 0, 0, s), "begin");
-  RLK_TRY(launch_advantage(R, rewards, group_ids, adv_eps, members, gstart, gidx, gsize, gmu, gsig, geq, adv, hdr, s),
+  RLK_TRY(launch_begin_advantage(R, rewards, group_ids, adv_eps, members, gstart, gidx, gsize, sort_a, sort_b, adv,
+                                 n_groups, hdr, nullptr, 0, s),
           "advantage");
-  if (n_groups)
-    RLK_TRY(hipMemcpyAsync(n_groups, &hdr->n_groups, sizeof(int32_t), hipMemcpyDeviceToDevice, s), "copy n_groups");
   return finish(hipSuccess, "", ws, s);
 }
 
@@ -537,10 +533,12 @@ rlk_status_t rlk_logprob_fwd(const rlk_batch_t* b, const void* hidden, const voi
   WsHeader* hdr = reinterpret_cast<WsHeader*>(w + L.hdr);
   const int64_t N = b->N;
 
-  RLK_TRY(launch_begin(reinterpret_cast<int32_t*>(hdr), b->cu_seqlens, b->R, N, s), "begin");
-  if (N == 0) return finish(hipSuccess, "", ws, s);
-  RLK_TRY(launch_compact(mask, b->cu_seqlens, nullptr, b->R, N, targets, b->V, b->max_policy_tokens, nullptr, w, L,
-                         s),
+  if (N == 0) {
+    RLK_TRY(launch_begin(reinterpret_cast<int32_t*>(hdr), b->cu_seqlens, b->R, N, s), "begin");
+    return finish(hipSuccess, "", ws, s);
+  }
+  RLK_TRY(launch_compact(mask, b->cu_seqlens, nullptr, b->R, N, targets, b->V, b->max_policy_tokens, nullptr, true, w,
+                         L, s),
           "compact");
   for (int c = 0; c < L.nchunks; ++c) {
     const int64_t c0 = (int64_t)c * L.Mc;
@@ -611,9 +609,8 @@ rlk_status_t rlk_compact(const rlk_batch_t* b, const uint8_t* mask, const int32_
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   char* w = static_cast<char*>(ws);
   WsHeader* hdr = reinterpret_cast<WsHeader*>(w + L.hdr);
-  RLK_TRY(launch_begin(reinterpret_cast<int32_t*>(hdr), b->cu_seqlens, b->R, b->N, s), "begin");
   RLK_TRY(launch_compact(mask, b->cu_seqlens, group_ids, b->R, b->N, targets, b->V, b->max_policy_tokens, nullptr,
-                         w, L, s),
+                         true, w, L, s),
           "compact");
   if (b->N > 0) {
     RLK_TRY(hipMemcpyAsync(idx, w + L.idx, (size_t)b->N * 4, hipMemcpyDeviceToDevice, s), "copy idx");
@@ -690,17 +687,16 @@ rlk_status_t rlk_pg_loss_fwd_bwd(const rlk_batch_t* b, const void* hidden, const
   auto F = [&](size_t off) { return reinterpret_cast<float*>(w + off); };
   auto I = [&](size_t off) { return reinterpret_cast<int32_t*>(w + off); };
 
-  RLK_TRY(launch_begin(reinterpret_cast<int32_t*>(hdr), b->cu_seqlens, R, N, s), "begin");
-  RLK_TRY(launch_advantage(R, rewards, group_ids, p->adv_eps, I(L.members), I(L.gstart), I(L.gidx), I(L.gsize),
-                           reinterpret_cast<double*>(w + L.gmu), reinterpret_cast<double*>(w + L.gsig), I(L.geq),
-                           F(L.adv), hdr, s),
+  RLK_TRY(launch_begin_advantage(R, rewards, group_ids, p->adv_eps, I(L.members), I(L.gstart), I(L.gidx), I(L.gsize),
+                                 reinterpret_cast<double*>(w + L.sort_a), reinterpret_cast<double*>(w + L.sort_b),
+                                 F(L.adv), nullptr, hdr, b->cu_seqlens, N, s),
           "advantage");
   // With the advantage-weighted surrogate as the only term (no entropy bonus, KL term or per-token
   // advantages), a rollout of advantage exactly 0 has an exactly zero gradient: its tokens go last in
   // the compacted list and the backward covers the tokens before them.
   const bool zero_grad_skip = p->entropy_coef == 0.0f && p->kl_coef == 0.0f && !p->token_adv;
   RLK_TRY(launch_compact(mask, b->cu_seqlens, group_ids, R, N, targets, b->V, b->max_policy_tokens,
-                         zero_grad_skip ? F(L.adv) : nullptr, w, L, s),
+                         zero_grad_skip ? F(L.adv) : nullptr, false, w, L, s),
           "compact");
   if (!L.w_kmajor)
     RLK_TRY(launch_transpose_w(b->dtype, W, w + L.wt, b->V, L.Vp, b->d, L.ldw, s), "transpose_w");

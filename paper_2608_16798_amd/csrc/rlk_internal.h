@@ -64,7 +64,7 @@ inline size_t splitk_bytes(int64_t mmax, int64_t n, const SplitK& p) {
   if (p.s < 2) return 0;
   return (size_t)p.s * (size_t)((mmax + kTile - 1) / kTile * kTile) * (size_t)((n + kTile - 1) / kTile * kTile) * 4;
 }
-constexpr int kScanTile = 4096;  // tokens per compaction block
+constexpr int kScanTile = 1024;  // tokens per compaction block
 constexpr int kMaxRollouts = 16384;
 constexpr int kRollSums = 8;     // per-rollout fp64 sums of the loss reduction
 
@@ -116,7 +116,8 @@ struct WsLayout {
   // compaction block scan [nblk]
   size_t blkcnt = 0, blkoff = 0;
   // rollouts [R]
-  size_t rstart = 0, rnpol = 0, members = 0, gstart = 0, gidx = 0, gsize = 0, gmu = 0, gsig = 0, geq = 0, adv = 0;
+  size_t rstart = 0, rnpol = 0, members = 0, gstart = 0, gidx = 0, gsize = 0, adv = 0;
+  size_t sort_a = 0, sort_b = 0;   // uint64 [R]: sort scratch of the advantages
   size_t rsum = 0;  // double [R][kRollSums]
   // chunk buffers
   size_t pm = 0, ps = 0, pu = 0;   // float [nvt][Mc]
@@ -152,14 +153,17 @@ struct WsLayout {
 hipError_t launch_begin(int32_t* status_hdr, const int32_t* cu, int R, int64_t N, hipStream_t s);
 // zero_adv [R] (may be NULL): the rollouts' advantages; the tokens of a rollout whose advantage is
 // exactly 0 are listed after all others (n_grad = the count before them; NULL: n_grad = n_eff).
+// begin: the header is reset and cu checked here as well (launch_begin's work).
 hipError_t launch_compact(const uint8_t* mask, const int32_t* cu, const int32_t* gid, int R, int64_t N,
-                          const int32_t* targets, int V, int32_t max_policy, const float* zero_adv, char* ws,
+                          const int32_t* targets, int V, int32_t max_policy, const float* zero_adv, bool begin, char* ws,
                           const WsLayout& L, hipStream_t s);
-// members [R] (rollouts of the kept groups, group by group), gstart [R + 1] (run starts), gidx [R],
-// and per group gsize, gmu, gsig, geq [R]; R <= kMaxRollouts.
-hipError_t launch_advantage(int R, const float* rewards, const int32_t* gid, float adv_eps, int32_t* members,
-                            int32_t* gstart, int32_t* gidx, int32_t* gsize, double* gmu, double* gsig, int32_t* geq,
-                            float* adv, WsHeader* hdr, hipStream_t s);
+// Header reset and cu check (cu may be NULL), then the group advantages: members [R] (rollouts of the kept
+// groups, group by group), gstart [R + 1] (run starts), gidx [R], gsize (per group), adv [R];
+// n_groups_out may be NULL; sort_a, sort_b: 8 bytes of scratch per rollout each.  R <= kMaxRollouts.
+hipError_t launch_begin_advantage(int R, const float* rewards, const int32_t* gid, float adv_eps, int32_t* members,
+                                  int32_t* gstart, int32_t* gidx, int32_t* gsize, double* sort_a, double* sort_b,
+                                  float* adv, int32_t* n_groups_out, WsHeader* hdr, const int32_t* cu, int64_t N,
+                                  hipStream_t s);
 
 // ---- launchers (k_token.hip) ----
 hipError_t launch_transpose_w(int dtype, const void* W, void* WT, int V, int64_t Vp, int d, int64_t ldw,

@@ -140,3 +140,42 @@ def test_value_head_row_and_column_splits(dtype, lens, d, accumulate):
     assert torch.equal(dw, dw1) and torch.equal(db, db1)
     if accumulate:
         assert torch.equal(dh[torch.as_tensor(on[:, 0] == 0, device="cuda")], dh0[torch.as_tensor(on[:, 0] == 0, device="cuda")])
+
+
+# one workgroup up to 1,024 rollouts; beyond, runs of 1,024 (whole, a short last one, all sixteen)
+@pytest.mark.parametrize("R,G", [(1, 1), (63, 4), (64, 64), (65, 1), (1023, 7), (1024, 1024), (1025, 3), (2048, 16),
+                                 (5000, 5000), (16384, 1), (16383, 97)])
+def test_group_advantage_run_edges(R, G):
+    ensure_library()
+    rng = np.random.default_rng(R + G)
+    gid = rng.permutation(np.arange(R) // G).astype(np.int32) * 5 + 2
+    gid[rng.random(R) < 0.05] = -3
+    rew = (rng.integers(0, 4, R) / 4).astype(np.float32)
+    idx, count = torch.full((R,), 9, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    adv = rlk.group_advantage(torch.as_tensor(rew, device="cuda"), torch.as_tensor(gid, device="cuda"), group_index=idx,
+                              n_groups=count)
+    ref = O.group_advantage(rew, gid, float(np.float32(1e-6)))
+    np.testing.assert_array_equal(to_host(idx), ref["group_index"])
+    assert int(count.item()) == ref["n_groups"]
+    a = to_host(adv).astype(np.float64)
+    # fp64 sums, one rounding to fp32
+    np.testing.assert_allclose(a, ref["adv"], rtol=2.0 ** -23, atol=1e-12)
+    assert np.all(a[ref["adv"] == 0] == 0)
+
+
+# 1,024 tokens per block, 4 per thread; above 1,024 blocks a scan launch instead of each block's own sums
+@pytest.mark.parametrize("N,R", [(1, 1), (1023, 3), (1024, 1), (1025, 2), (4099, 1000), (1 << 20, 7), ((1 << 20) + 1, 5)])
+def test_compaction_block_edges(N, R):
+    ensure_library()
+    rng = np.random.default_rng(N)
+    cu = np.concatenate([[0], np.sort(rng.integers(0, N + 1, R - 1)), [N]]).astype(np.int32)
+    mask = (rng.random(N) < 0.4).astype(np.uint8)
+    gid = rng.integers(-1, 3, R).astype(np.int32)
+    d = lambda a: torch.as_tensor(a, device="cuda")
+    idx, tokr, n_pol, n_eff, ws = rlk.compact(d(cu), d(mask), d(gid))
+    widx, wtokr, wn = O.compact(mask, cu, gid)
+    n = int(n_eff.item())
+    assert n == widx.size and rlk.check_status(ws) == 0
+    np.testing.assert_array_equal(to_host(idx)[:n], widx)
+    np.testing.assert_array_equal(to_host(tokr)[:n], wtokr)
+    np.testing.assert_array_equal(to_host(n_pol), wn)
