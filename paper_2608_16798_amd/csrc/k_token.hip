@@ -212,57 +212,93 @@ __global__ void __launch_bounds__(256) k_hidden_t(const uint16_t* hc, int d, con
 }
 
 // ---- merge of the per-vocabulary-tile partials (m, s, u) into lse, logp, H; loss scalars.
-__global__ void __launch_bounds__(256) k_combine(TokenParams p) {
-  // 64 tokens per block; wavefront w merges the vocabulary tiles k = w, w + 4, ... of its lane's
-  // token (loads coalesced over the 64 tokens) in one pass with a running maximum M_w:
-  //   S_w = sum_k e^{m_k - M_w} s_k,  T_w = sum_k e^{m_k - M_w} (u_k + (m_k - M_w) s_k),
-  // rescaled by e^{M_w - M'} (and T_w shifted by (M_w - M') S_w) whenever the maximum grows to M';
-  // the four wavefront results meet in LDS the same way.  Then lse = M + ln S and
-  // sum_j p_j (z_j - lse) = T / S - ln S.
-  __shared__ float s_m[4][64];
-  __shared__ double s_S[4][64], s_T[4][64];
+// A block of 16 wavefronts merges TOK tokens: a wavefront holds 64 / TOK strides of vocabulary tiles, and a
+// lane merges the tiles k = stride, stride + G, ... (G = 16 * 64 / TOK) of its token, kBatch tiles' loads in
+// flight, with a running maximum M:
+//   S = sum_k e^{m_k - M} s_k,  T = sum_k e^{m_k - M} (u_k + (m_k - M) s_k),
+// rescaled by e^{M - M'} (and T shifted by (M - M') S) whenever a batch raises the maximum to M'; the
+// strides meet by shuffles, then in LDS, the same way.  Then lse = M + ln S and
+// sum_j p_j (z_j - lse) = T / S - ln S.
+// Bound by the latency of the loads: few tokens are dealt in blocks of 16, with 64 strides of tiles side by
+// side, many in blocks of 64, whose loads are whole lines.  Against blocks of 64 tokens on four wavefronts, one
+// tile in flight: 160 tokens of 594 tiles 107 -> 9 us, 770 tokens 127 -> 14 us, 23,000 tokens of 196 tiles 52 -> 20 us.
+constexpr int kCombineWaves = 16;
+
+// (M, S, T) += (m, s, t), both relative to their own maximum (-inf: no tile, sums of 0, or of NaN where all
+// its logits are, which stays in the sums)
+__device__ __forceinline__ void merge_partial(float& M, double& S, double& T, float m, double s, double t) {
+  const float n = fmaxf(M, m);
+  const float da = M == -INFINITY ? 0.0f : M - n, db = m == -INFINITY ? 0.0f : m - n;
+  const double fa = (double)__builtin_amdgcn_exp2f(da * kLog2e), fb = (double)__builtin_amdgcn_exp2f(db * kLog2e);
+  T = fa * (T + (double)da * S) + fb * (t + (double)db * s);
+  S = fa * S + fb * s;
+  M = n;
+}
+
+template <int TOK>
+__global__ void __launch_bounds__(64 * kCombineWaves) k_combine(TokenParams p) {
+  constexpr int kBatch = 4;
+  constexpr int SUB = 64 / TOK, G = SUB * kCombineWaves;
+  __shared__ float s_m[kCombineWaves][TOK];
+  __shared__ double s_S[kCombineWaves][TOK], s_T[kCombineWaves][TOK];
   int64_t rc = (int64_t)p.hdr->n_eff - p.c0;
   rc = rc < 0 ? 0 : (rc > p.Mc ? p.Mc : rc);
+  if ((int64_t)blockIdx.x * TOK >= rc) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t tl = (int64_t)blockIdx.x * 64 + lane;
-  if ((int64_t)blockIdx.x * 64 >= rc) return;
+  const int tok = lane % TOK;
+  const int64_t tl = (int64_t)blockIdx.x * TOK + tok;
   const bool act = tl < rc;
-  float Mw = -INFINITY;
+  float M = -INFINITY;
   double S = 0.0, T = 0.0;
   if (act)
-    for (int k = wv; k < p.nvt; k += 4) {
-      const int64_t o = (int64_t)k * p.Mc + tl;
-      const float mk = p.pm[o];
-      const double sk = (double)p.ps[o];
-      const double uk = (double)p.pu[o];
-      if (mk > Mw) {
-        if (Mw > -INFINITY) {
-          const double f = (double)__builtin_amdgcn_exp2f((Mw - mk) * kLog2e);
-          T = f * (T + (double)(Mw - mk) * S);
+    for (int k0 = wv * SUB + lane / TOK; k0 < p.nvt; k0 += kBatch * G) {
+      float mk[kBatch], sk[kBatch], uk[kBatch];
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        const int k = k0 + j * G;
+        const int64_t o = (int64_t)(k < p.nvt ? k : k0) * p.Mc + tl;
+        mk[j] = p.pm[o];
+        sk[j] = p.ps[o];
+        uk[j] = p.pu[o];
+        if (k >= p.nvt) mk[j] = -INFINITY;
+      }
+      float n = M;
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) n = fmaxf(n, mk[j]);
+      if (n > M) {
+        if (M > -INFINITY) {
+          const double f = (double)__builtin_amdgcn_exp2f((M - n) * kLog2e);
+          T = f * (T + (double)(M - n) * S);
           S *= f;
         }
-        Mw = mk;
+        M = n;
       }
-      const double w = (double)__builtin_amdgcn_exp2f((mk - Mw) * kLog2e);
-      S += w * sk;
-      T += w * (uk + (double)(mk - Mw) * sk);
-    }
-  s_m[wv][lane] = Mw;
-  s_S[wv][lane] = S;
-  s_T[wv][lane] = T;
-  __syncthreads();
-  if (wv != 0 || !act) return;
-  const float M = fmaxf(fmaxf(s_m[0][lane], s_m[1][lane]), fmaxf(s_m[2][lane], s_m[3][lane]));
-  S = 0.0;
-  T = 0.0;
 #pragma unroll
-  for (int w4 = 0; w4 < 4; ++w4) {
-    const float mw = s_m[w4][lane];
-    if (mw == -INFINITY) continue;  // a wavefront without vocabulary tiles (fewer than 4 tiles)
-    const double f = (double)__builtin_amdgcn_exp2f((mw - M) * kLog2e);
-    S += f * s_S[w4][lane];
-    T += f * (s_T[w4][lane] + (double)(mw - M) * s_S[w4][lane]);
+      for (int j = 0; j < kBatch; ++j) {
+        if (k0 + j * G >= p.nvt) break;
+        const double w = (double)__builtin_amdgcn_exp2f((mk[j] - M) * kLog2e);
+        S += w * (double)sk[j];
+        T += w * ((double)uk[j] + (double)(mk[j] - M) * (double)sk[j]);
+      }
+    }
+#pragma unroll
+  for (int o = TOK; o < 64; o <<= 1) {
+    const float m = __shfl_xor(M, o, 64);
+    const double s = __shfl_xor(S, o, 64), t = __shfl_xor(T, o, 64);
+    merge_partial(M, S, T, m, s, t);
   }
+  if (lane < TOK) {
+    s_m[wv][lane] = M;
+    s_S[wv][lane] = S;
+    s_T[wv][lane] = T;
+  }
+  __syncthreads();
+  if (wv != 0 || lane >= TOK || !act) return;
+  M = s_m[0][lane];
+  S = s_S[0][lane];
+  T = s_T[0][lane];
+#pragma unroll
+  for (int k = 1; k < kCombineWaves; ++k) merge_partial(M, S, T, s_m[k][lane], s_S[k][lane], s_T[k][lane]);
   const int64_t i = p.c0 + tl;
   const double lnS = log(S);
   const double lse = (double)M + lnS;
@@ -629,7 +665,9 @@ hipError_t launch_hidden_t(const void* hc, int d, const float* st, const int32_t
 
 hipError_t launch_combine(const TokenParams& p, hipStream_t s) {
   prof_mark(KK_COMBINE, true, s);
-  k_combine<<<(unsigned)((p.Mc + 63) / 64), 256, 0, s>>>(p);
+  // 16 tokens per block up to the rows that give each compute unit one block
+  if (p.Mc <= 16 * 256) k_combine<16><<<(unsigned)((p.Mc + 15) / 16), 64 * kCombineWaves, 0, s>>>(p);
+  else k_combine<64><<<(unsigned)((p.Mc + 63) / 64), 64 * kCombineWaves, 0, s>>>(p);
   prof_mark(KK_COMBINE, false, s);
   return hipGetLastError();
 }

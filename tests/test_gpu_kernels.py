@@ -179,3 +179,24 @@ def test_compaction_block_edges(N, R):
     np.testing.assert_array_equal(to_host(idx)[:n], widx)
     np.testing.assert_array_equal(to_host(tokr)[:n], wtokr)
     np.testing.assert_array_equal(to_host(n_pol), wn)
+
+
+# the merge of the vocabulary tiles: blocks of 16 tokens up to 4,096 chunk rows and of 64 above, tiles dealt in
+# strides of 64 or 16 and batches of four: fewer tiles than strides, one past a batch, several batches
+@pytest.mark.parametrize("tokens,V", [(1, 64 * 256 + 1), (15, 300), (17, 257 * 256), (4096, 15 * 256 + 3), (4097, 17 * 256),
+                                      (4200, 65 * 256 + 1)])
+def test_combine_strides(tokens, V):
+    ensure_library()
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    h, W = (torch.randn(n, 64, generator=gen, device="cuda").bfloat16() for n in (tokens, V))
+    W[V // 2] *= 4  # the largest logits lie in one tile
+    y = torch.randint(0, V, (tokens,), generator=gen, device="cuda", dtype=torch.int32)
+    cu, mask = torch.tensor([0, tokens], dtype=torch.int32, device="cuda"), torch.ones(tokens, dtype=torch.uint8, device="cuda")
+    logp, ent = torch.empty(tokens, device="cuda"), torch.empty(tokens, device="cuda")
+    rlk.logprob_fwd(h, W, y, mask, cu, logp=logp, entropy=ent)
+    for r in range(0, tokens, 1024):
+        z = torch.log_softmax(h[r:r + 1024].double() @ W.double().T, 1)
+        lp, H = z.gather(1, y[r:r + 1024, None].long())[:, 0], -(z.exp() * z).sum(1)
+        # fp32 logits of up to 64 products, |z| up to about 100; one rounding of the results
+        for got, want in ((logp, lp), (ent, H)):
+            assert float((got[r:r + 1024].double() - want).abs().max()) <= 2.0 ** -23 * 100 * 4
