@@ -62,7 +62,7 @@ __device__ __forceinline__ int qswz(int t) { return (t >> 3) & 7; }
 constexpr int LDS_B = RED_OFF + 3 * WAVES_M * kTile * 4;
 static_assert(LDS_B >= PIPE_B && LDS_B <= 163840, "LDS of a compute unit");
 constexpr int GROUP_M = 16;
-constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 constexpr int kBufferFlags = 0x00020000;  // raw buffer: 32-bit data format, offset range-checked
 
 #define LDSP(p) ((__attribute__((address_space(3))) void*)(p))
@@ -541,7 +541,6 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
     }
     const int v0 = tile_m * kTile;
     const int V = a.V;
-    const bool full_v = v0 + kTile <= V;
     // q and q^T are read only for the tokens with a surrogate gradient (the first n_grad of the
     // list): the stores stop there (q^T writes zero columns up to the K pad)
     int ng = N;
@@ -553,91 +552,100 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
     float* red_s = red_m + WAVES_M * kTile;                    // [WAVES_M][256]
     float* red_u = red_s + WAVES_M * kTile;                    // [WAVES_M][256]
 
-    // phase 1: per-token max over this tile's 256 vocabulary rows; gather the target logit.
-#pragma unroll
-    for (int cb = 0; cb < 2 * NB; ++cb) {
-      const int hb = cb / NB, nb = cb % NB;
-      const int cl = hb * HALF + wn * WTN + nb * 16 + lr;
-      const int n = tile_n * kTile + cl;
-      float mx = -INFINITY;
-#pragma unroll
-      for (int rb = 0; rb < 2 * MB; ++rb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int rl = (rb / MB) * HALF + wm * WTM + (rb % MB) * 16 + 4 * lg + r;
-          const float z = (full_v || v0 + rl < V) ? acc[rb / MB][hb][rb % MB][nb][r] : -INFINITY;
-          mx = fmaxf(mx, z);
-        }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      if (lg == 0) red_m[wm * kTile + cl] = mx;
-      if (n < N) {
-        const int y = a.ytgt[a.c0 + n];
-        const int yl = y - v0;
-        if (y >= 0 && y < V && yl >= 0 && yl < kTile && ((yl / WTM) & 1) == wm && ((yl >> 2) & 3) == lg) {
-          const int trb = (yl / HALF) * MB + (yl % WTM) / 16, tr = yl & 3;
-          float z = 0.0f;
-#pragma unroll
-          for (int rb = 0; rb < 2 * MB; ++rb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) z = (rb == trb && r == tr) ? acc[rb / MB][hb][rb % MB][nb][r] : z;
-          a.zy[a.c0 + n] = z;
-        }
-      }
-    }
-    __syncthreads();
-
-    // phase 2: e = exp(z - c), s = sum e, u = sum e (z - c) against the token's reference c (the
-    // tile maximum m, or with a.zr the reference logit r clamped to m - kRefSpan); e optionally
-    // staged for storage.
     char* sQ = smem;
+    // Phases 1 and 2, bound by the vector ALU (128 elements per lane): a tile of 256 vocabulary rows (all but
+    // the last) takes them without the row checks and u reuses e's exponent.  The forward of 38,900 tokens, d =
+    // 2048, V = 32,768: 4.44 -> 4.30 ms; log-probs of 49,000 tokens, d = 5120, V = 151,936: 54.2 -> 53.1 ms.
+    auto stats = [&](auto FULL) {
+      // phase 1: per-token max over this tile's 256 vocabulary rows; gather the target logit.
 #pragma unroll
-    for (int cb = 0; cb < 2 * NB; ++cb) {
-      const int hb = cb / NB, nb = cb % NB;
-      const int cl = hb * HALF + wn * WTN + nb * 16 + lr;
-      float mt = red_m[cl];
+      for (int cb = 0; cb < 2 * NB; ++cb) {
+        const int hb = cb / NB, nb = cb % NB;
+        const int cl = hb * HALF + wn * WTN + nb * 16 + lr;
+        const int n = tile_n * kTile + cl;
+        float mx = -INFINITY;
 #pragma unroll
-      for (int w = 1; w < WAVES_M; ++w) mt = fmaxf(mt, red_m[w * kTile + cl]);
-      const float ref = tile_ref(a, mt, tile_n * kTile + cl, N, true);
-      const float mt2 = ref * kLog2e;
-      float s = 0.0f, u = 0.0f;
+        for (int rb = 0; rb < 2 * MB; ++rb)
 #pragma unroll
-      for (int rb = 0; rb < 2 * MB; ++rb) {
-        const int rl0 = (rb / MB) * HALF + wm * WTM + (rb % MB) * 16 + 4 * lg;
-        float ev[4];
+          for (int r = 0; r < 4; ++r) {
+            const int rl = (rb / MB) * HALF + wm * WTM + (rb % MB) * 16 + 4 * lg + r;
+            const float z = (decltype(FULL)::value || v0 + rl < V) ? acc[rb / MB][hb][rb % MB][nb][r] : -INFINITY;
+            mx = fmaxf(mx, z);
+          }
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        if (lg == 0) red_m[wm * kTile + cl] = mx;
+        if (n < N) {
+          const int y = a.ytgt[a.c0 + n];
+          const int yl = y - v0;
+          if (y >= 0 && y < V && yl >= 0 && yl < kTile && ((yl / WTM) & 1) == wm && ((yl >> 2) & 3) == lg) {
+            const int trb = (yl / HALF) * MB + (yl % WTM) / 16, tr = yl & 3;
+            float z = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float z = acc[rb / MB][hb][rb % MB][nb][i];
-          const bool valid = full_v || v0 + rl0 + i < V;
-          const float e = valid ? __builtin_amdgcn_exp2f(fmaf(z, kLog2e, -mt2)) : 0.0f;
-          s += e;
-          u = fmaf(e, z - ref, u);
-          ev[i] = e;
-        }
-        if constexpr (STORE_Q) {
-          if constexpr (sizeof(T) == 2) {
-            u32x2 pk;
-            pk.x = pack_bf16x2(ev[0], ev[1]);
-            pk.y = pack_bf16x2(ev[2], ev[3]);
-            *reinterpret_cast<u32x2*>(sQ + cl * QROW + (((rl0 >> 3) ^ qswz(cl)) << 4) + (rl0 & 7) * 2) = pk;
-          } else {
-            const int n = tile_n * kTile + cl;
-            if (n < ng) {
-              float* qp = reinterpret_cast<float*>(a.q) + (int64_t)n * a.ldq + v0 + rl0;
-              store4(qp, f32x4{ev[0], ev[1], ev[2], ev[3]});
-            }
+            for (int rb = 0; rb < 2 * MB; ++rb)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) z = (rb == trb && r == tr) ? acc[rb / MB][hb][rb % MB][nb][r] : z;
+            a.zy[a.c0 + n] = z;
           }
         }
       }
-      s += __shfl_xor(s, 16, 64);
-      u += __shfl_xor(u, 16, 64);
-      s += __shfl_xor(s, 32, 64);
-      u += __shfl_xor(u, 32, 64);
-      if (lg == 0) {
-        red_s[wm * kTile + cl] = s;
-        red_u[wm * kTile + cl] = u;
+      __syncthreads();
+
+      // phase 2: e = exp(z - c), s = sum e, u = sum e (z - c) against the token's reference c (the
+      // tile maximum m, or with a.zr the reference logit r clamped to m - kRefSpan); e optionally
+      // staged for storage.  u sums the exponents of 2 that e is formed from, so the rounding of c log2(e)
+      // shifts ln s and u / s alike and leaves the entropy.
+#pragma unroll
+      for (int cb = 0; cb < 2 * NB; ++cb) {
+        const int hb = cb / NB, nb = cb % NB;
+        const int cl = hb * HALF + wn * WTN + nb * 16 + lr;
+        float mt = red_m[cl];
+#pragma unroll
+        for (int w = 1; w < WAVES_M; ++w) mt = fmaxf(mt, red_m[w * kTile + cl]);
+        const float ref = tile_ref(a, mt, tile_n * kTile + cl, N, true);
+        const float mt2 = ref * kLog2e;
+        float s = 0.0f, u = 0.0f;
+#pragma unroll
+        for (int rb = 0; rb < 2 * MB; ++rb) {
+          const int rl0 = (rb / MB) * HALF + wm * WTM + (rb % MB) * 16 + 4 * lg;
+          float ev[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float z = acc[rb / MB][hb][rb % MB][nb][i];
+            const bool valid = decltype(FULL)::value || v0 + rl0 + i < V;
+            const float t = fmaf(z, kLog2e, -mt2);
+            const float e = valid ? __builtin_amdgcn_exp2f(t) : 0.0f;
+            s += e;
+            u = fmaf(e, t, u);
+            ev[i] = e;
+          }
+          if constexpr (STORE_Q) {
+            if constexpr (sizeof(T) == 2) {
+              u32x2 pk;
+              pk.x = pack_bf16x2(ev[0], ev[1]);
+              pk.y = pack_bf16x2(ev[2], ev[3]);
+              *reinterpret_cast<u32x2*>(sQ + cl * QROW + (((rl0 >> 3) ^ qswz(cl)) << 4) + (rl0 & 7) * 2) = pk;
+            } else {
+              const int n = tile_n * kTile + cl;
+              if (n < ng) {
+                float* qp = reinterpret_cast<float*>(a.q) + (int64_t)n * a.ldq + v0 + rl0;
+                store4(qp, f32x4{ev[0], ev[1], ev[2], ev[3]});
+              }
+            }
+          }
+        }
+        s += __shfl_xor(s, 16, 64);
+        u += __shfl_xor(u, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        u += __shfl_xor(u, 32, 64);
+        if (lg == 0) {
+          red_s[wm * kTile + cl] = s;
+          red_u[wm * kTile + cl] = u * kLn2;
+        }
       }
-    }
+    };
+    if (v0 + kTile <= V) stats(std::true_type{});
+    else stats(std::false_type{});
     __syncthreads();
     if (wm == 0 && lg == 0) {
 #pragma unroll
