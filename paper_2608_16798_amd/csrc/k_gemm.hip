@@ -122,10 +122,6 @@ struct Op<float> {
   }
 };
 
-__device__ __forceinline__ uint16_t bf16_bits(float x) {
-  return __builtin_bit_cast(uint16_t, (__bf16)x);
-}
-
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   bf16x2 v;
   v.x = (__bf16)lo;
@@ -138,8 +134,6 @@ __device__ __forceinline__ void store4(float* p, f32x4 v) { *reinterpret_cast<f3
 __device__ __forceinline__ void store4(bf16_t* p, f32x4 v) {
   *reinterpret_cast<u32x2*>(p) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
 }
-__device__ __forceinline__ void store_elem(float* p, float x) { *p = x; }
-__device__ __forceinline__ void store_elem(bf16_t* p, float x) { p->bits = bf16_bits(x); }
 
 // XCD-aware tile mapping.  Workgroup ids are dispatched round-robin over the 8 XCDs, so the 256
 // workgroups resident at a time are 256 consecutive ids.  Tiles are rastered in column groups of
@@ -721,8 +715,253 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
   }
 }
 
+// ---- fp32 operands, few output tiles: a 256 x 64 tile per workgroup of four wavefronts, wavefront w the
+// 64 x 64 block of its rows 64 w .. + 63 in 32 x 32 MFMA blocks.  A small fp32 call is bound by the fp32 matrix
+// rate (1/16 of bf16) and by the compute units without a tile; a slice's MFMAs take 4,096 cycles of a SIMD, so
+// one barrier per slice and copies one slice ahead hide the memory.  1,024 tokens, d = 256, V = 4,096, against
+// 256 x 256 tiles: forward 75 -> 29 us (64 -> 256 tiles), dhidden 43 -> 27 us, dW 43 -> 26 us.
+constexpr int F_MB = kTile / 4 / 32, F_NB = 2;  // 32x32 MFMA blocks of a wavefront
+using f32x16 = float __attribute__((ext_vector_type(16)));
+
+template <int EPI, bool STORE_Q>
+__global__ void __launch_bounds__(256, 2) k_gemm_f32(GemmArgs a) {
+  constexpr int TN = kTileN32;
+  constexpr int F_NW = 4;                     // wavefronts, 64 rows each
+  constexpr int F_ROWS = kTile + TN;          // rows of a slice in LDS: A, then B
+  constexpr int F_BUF = F_ROWS * KS;
+  constexpr int F_IPW = F_ROWS / RPI / F_NW;  // copies of a slice per wavefront
+  static_assert(F_ROWS % (RPI * F_NW) == 0 && kTile % (RPI * F_NW) == 0, "a copy is of one operand");
+  __shared__ __attribute__((aligned(16))) char smem[2 * F_BUF];
+  int M = a.M, N = a.N, K = a.K;
+  int64_t rc = (int64_t)(EPI == EPI_FWD ? a.hdr->n_eff : a.hdr->n_grad) - a.c0;
+  rc = rc < 0 ? 0 : (rc > a.Mc ? a.Mc : rc);
+  if (EPI == EPI_FWD) N = (int)rc;
+  if (EPI == EPI_DH) M = (int)rc;
+  if (EPI == EPI_DW) {
+    if (rc == 0 && a.c0 > 0) return;  // nothing to add from an empty chunk
+    K = (int)((rc + kKAlign - 1) / kKAlign * kKAlign);
+  }
+  if (M <= 0 || N <= 0) return;
+  const int tm = (M + kTile - 1) / kTile, tn = (N + TN - 1) / TN;
+  int tile_m, tile_n;
+  if (!map_tile(tm, tn, tile_m, tile_n)) return;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lh = lane >> 5;
+  const int row0 = tile_m * kTile, col0 = tile_n * TN;
+
+  // operand panels as in k_gemm: rows beyond M / N and K chunks beyond K read as zero
+  const uint32_t lda_b = (uint32_t)(a.lda * 4), ldb_b = (uint32_t)(a.ldb * 4);
+  const int rows_a = min(kTile, M - row0), rows_b = min(TN, N - col0);
+  char* const pa = const_cast<char*>(reinterpret_cast<const char*>(a.A) + (int64_t)row0 * lda_b);
+  char* const pb = const_cast<char*>(reinterpret_cast<const char*>(a.B) + (int64_t)col0 * ldb_b);
+  const int64_t Kb = (int64_t)K * 4;
+  int nk = (int)((Kb + KS - 1) / KS);
+  int ks0 = 0;
+  if (EPI != EPI_FWD && a.ksplit > 1) {
+    ks0 = (int)blockIdx.y * a.kslices;
+    nk = max(0, min(nk, ks0 + a.kslices) - ks0);
+  }
+  const __amdgpu_buffer_rsrc_t ra =
+      __builtin_amdgcn_make_buffer_rsrc(pa, (short)0, (int)((uint32_t)rows_a * lda_b), kBufferFlags);
+  const __amdgpu_buffer_rsrc_t rb =
+      __builtin_amdgcn_make_buffer_rsrc(pb, (short)0, (int)((uint32_t)rows_b * ldb_b), kBufferFlags);
+  // copy j of this wavefront: rows 8 (wid + F_NW j) .. + 7 of the slice's F_ROWS (A's rows, then B's); lane l
+  // carries row l / 8 of them into LDS slot l % 8, which holds the K chunk (l % 8) ^ swz(row)
+  auto copy_slice = [&](int kt, int buf) {
+    const uint32_t kb = (uint32_t)(kt + ks0) * KS;
+#pragma unroll
+    for (int j = 0; j < F_IPW; ++j) {
+      const int r8 = (wid + F_NW * j) * RPI;
+      const bool is_b = j >= kTile / (RPI * F_NW);
+      const int r = (is_b ? r8 - kTile : r8), row = r + lane / CPR;
+      const int chunk = (lane % CPR) ^ swz(row);
+      uint32_t o = (uint32_t)(lane / CPR) * (is_b ? ldb_b : lda_b) + chunk * 16;
+      if (row >= (is_b ? rows_b : rows_a) || (int64_t)kb + chunk * 16 >= Kb) o = 0x80000000u;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(is_b ? rb : ra, LDSP(smem + buf * F_BUF + r8 * KS), 16, o,
+                                               kb + (uint32_t)r * (is_b ? ldb_b : lda_b), 0, 0);
+    }
+  };
+
+  // two sums per output, of the even and the odd halves of the slices (shorter fp32 chains)
+  f32x16 acc[F_MB][F_NB] = {}, acc1[F_MB][F_NB] = {};
+  // half hs of a slice: lane (lr, lh) holds chunks 4 hs + lh and 4 hs + 2 + lh of row lr of each 32-row block
+  u32x4 fa[F_MB][2][2], fb[F_NB][2][2];
+  auto read = [&](int buf, int hs) {
+    const char* base = smem + buf * F_BUF;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int ch = ((4 * hs + 2 * c + lh) ^ swz(lr)) * 16;
+#pragma unroll
+      for (int mb = 0; mb < F_MB; ++mb)
+        fa[mb][hs][c] = *reinterpret_cast<const u32x4*>(base + (wid * 64 + mb * 32 + lr) * KS + ch);
+#pragma unroll
+      for (int nb = 0; nb < F_NB; ++nb)
+        fb[nb][hs][c] = *reinterpret_cast<const u32x4*>(base + (kTile + nb * 32 + lr) * KS + ch);
+    }
+  };
+  auto mma = [&](f32x16 (&d)[F_MB][F_NB], int hs) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int mb = 0; mb < F_MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < F_NB; ++nb) {
+          const float x = __uint_as_float(fa[mb][hs][e / 4][e % 4]), y = __uint_as_float(fb[nb][hs][e / 4][e % 4]);
+          d[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(EPI == EPI_FWD ? x : y, EPI == EPI_FWD ? y : x, d[mb][nb],
+                                                           0, 0, 0);
+        }
+  };
+  // Each half of a slice is read under the MFMAs of the half before it.  At the barrier in the middle of slice
+  // kt, slice kt + 1 has landed and every wavefront holds the second half of slice kt, whose buffer the copies
+  // of slice kt + 2 take.
+  if (nk > 0) {
+    copy_slice(0, 0);
+    wait_vmcnt<0>();
+    block_barrier();
+    read(0, 0);
+    if (nk > 1) copy_slice(1, 1);
+  }
+  for (int kt = 0; kt < nk; ++kt) {
+    const int buf = kt & 1;
+    read(buf, 1);
+    mma(acc, 0);
+    wait_vmcnt<0>();
+    wait_lgkm0();
+    block_barrier();
+    if (kt + 1 < nk) read(buf ^ 1, 0);
+    if (kt + 2 < nk) copy_slice(kt + 2, buf);
+    mma(acc1, 1);
+  }
+#pragma unroll
+  for (int i = 0; i < F_MB * F_NB; ++i) acc[i / F_NB][i % F_NB] += acc1[i / F_NB][i % F_NB];
+  // Block D = X Y^T: lane (lr, lh) holds column lr (a row of Y), register 4 g + r row 8 g + 4 lh + r (of X)
+  auto four = [&](int mb, int nb, int g) {
+    const f32x16& d = acc[mb][nb];
+    return f32x4{d[4 * g], d[4 * g + 1], d[4 * g + 2], d[4 * g + 3]};
+  };
+
+  if constexpr (EPI != EPI_FWD) {
+    // rows row0 + 64 wid + 32 mb + lr, columns (features) col0 + 32 nb + 8 g + 4 lh + 0..3
+    const bool add = EPI == EPI_DW && (a.accumulate || a.c0 > 0);
+    const bool wide = EPI == EPI_DH || (reinterpret_cast<uintptr_t>(a.dw) & 15) == 0;
+#pragma unroll
+    for (int mb = 0; mb < F_MB; ++mb) {
+      const int m = row0 + wid * 64 + mb * 32 + lr;
+      if (m >= M) continue;
+      float* out;
+      if (a.ksplit > 1) out = a.part + ((int64_t)blockIdx.y * a.mp + m) * a.ldp;
+      else if constexpr (EPI == EPI_DH) out = reinterpret_cast<float*>(a.out) + (int64_t)a.idx[a.c0 + m] * a.ldo;
+      else out = a.dw + (int64_t)m * a.ldo;
+#pragma unroll
+      for (int i = 0; i < 4 * F_NB; ++i) {
+        const int n = col0 + i * 8 + 4 * lh;
+        if (n >= N) continue;
+        const f32x4 v = four(mb, i / 4, i % 4);
+        if (a.ksplit > 1 || (wide && !add)) {
+          store4(out + n, v);
+        } else if (wide) {
+          store4(out + n, *reinterpret_cast<const f32x4*>(out + n) + v);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) out[n + r] = add ? out[n + r] + v[r] : v[r];
+        }
+      }
+    }
+  } else {
+    // vocabulary rows v = row0 + rl, rl = 64 wid + 8 i + 4 lh + r, i = 4 mb + g; token columns n = col0 + 32 nb + lr
+    const int V = a.V;
+    int ng = N;
+    if constexpr (STORE_Q) {
+      const int64_t g = (int64_t)a.hdr->n_grad - a.c0;
+      ng = g < 0 ? 0 : (g < N ? (int)g : N);
+    }
+    block_barrier();  // the reduction reuses the LDS of the pipeline
+    float* red_m = reinterpret_cast<float*>(smem);  // [4][TN]
+    float* red_s = red_m + 4 * TN;
+    float* red_u = red_s + 4 * TN;
+#pragma unroll
+    for (int nb = 0; nb < F_NB; ++nb) {
+      const int cl = nb * 32 + lr, n = col0 + cl;
+      float mx = -INFINITY;
+#pragma unroll
+      for (int mb = 0; mb < F_MB; ++mb) {
+        acc[mb][nb] *= a.inv_tau;
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (row0 + wid * 64 + mb * 32 + 8 * (e / 4) + 4 * lh + e % 4 < V) mx = fmaxf(mx, acc[mb][nb][e]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      if (lh == 0) red_m[wid * TN + cl] = mx;
+      if (n < N) {
+        // the target's logit, if it is one of this lane's
+        const int y = a.ytgt[a.c0 + n], yl = y - row0;
+        if (y >= 0 && y < V && yl >= 0 && yl < kTile && (yl >> 6) == wid && ((yl >> 2) & 1) == lh) {
+          float z = 0.0f;
+#pragma unroll
+          for (int mb = 0; mb < F_MB; ++mb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+              z = (mb == ((yl >> 5) & 1) && e / 4 == ((yl >> 3) & 3) && e % 4 == (yl & 3)) ? acc[mb][nb][e] : z;
+          a.zy[a.c0 + n] = z;
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int nb = 0; nb < F_NB; ++nb) {
+      const int cl = nb * 32 + lr, n = col0 + cl;
+      float m = red_m[cl];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) m = fmaxf(m, red_m[w * TN + cl]);
+      const float m2 = m * kLog2e;
+      float s = 0.0f, u = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4 * F_MB; ++i) {
+        const int rl = wid * 64 + i * 8 + 4 * lh;
+        const f32x4 z = four(i / 4, nb, i % 4);
+        f32x4 e4;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float t = fmaf(z[r], kLog2e, -m2);
+          const float e = row0 + rl + r < V ? __builtin_amdgcn_exp2f(t) : 0.0f;
+          s += e;
+          u = fmaf(e, t, u);
+          e4[r] = e;
+        }
+        if constexpr (STORE_Q)
+          if (n < ng) store4(reinterpret_cast<float*>(a.q) + (int64_t)n * a.ldq + row0 + rl, e4);
+      }
+      s += __shfl_xor(s, 32, 64);
+      u += __shfl_xor(u, 32, 64);
+      if (lh == 0) {
+        red_s[wid * TN + cl] = s;
+        red_u[wid * TN + cl] = u * kLn2;
+      }
+    }
+    __syncthreads();
+    const int n = col0 + tid;
+    if (tid < TN && n < N) {
+      float m = red_m[tid], s = red_s[tid], u = red_u[tid];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) {
+        m = fmaxf(m, red_m[w * TN + tid]);
+        s += red_s[w * TN + tid];
+        u += red_u[w * TN + tid];
+      }
+      const int64_t o = (int64_t)tile_m * a.Mc + n;
+      a.pm[o] = m;
+      a.ps[o] = s;
+      a.pu[o] = u;
+    }
+  }
+}
+
 // Split-K reduction: out = sum of the partials in split order (deterministic), then the dhidden
-// scatter or the dW overwrite / accumulate.  Rows and the empty-chunk rule follow the GEMM.
+// scatter or the dW overwrite / accumulate.  Rows and the empty-chunk rule follow the GEMM.  HBM bound:
+// four outputs per thread (N is a multiple of 8), four splits' loads in flight.  A split launch has fewer
+// than 256 tiles and the rest of a tile row, so 32 bits count its groups of four.
 template <typename T, int EPI>
 __global__ void __launch_bounds__(256) k_splitk_reduce(GemmArgs a) {
   int64_t rc = (int64_t)a.hdr->n_grad - a.c0;
@@ -730,37 +969,51 @@ __global__ void __launch_bounds__(256) k_splitk_reduce(GemmArgs a) {
   int M = a.M;
   if (EPI == EPI_DH) M = (int)rc;
   if (EPI == EPI_DW && rc == 0 && a.c0 > 0) return;
-  const int N = a.N;
-  const int64_t total = (int64_t)M * N;
+  const uint32_t N4 = (uint32_t)a.N / 4, total = (uint32_t)M * N4;
   const bool add = EPI == EPI_DW && (a.accumulate || a.c0 > 0);
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t m = e / N, n = e - m * N;
-    float acc = 0.0f;
-    for (int y = 0; y < a.ksplit; ++y) acc += a.part[((int64_t)y * a.mp + m) * a.ldp + n];
+  const int64_t step = a.mp * a.ldp;
+  for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
+    const uint32_t m = e / N4, n = (e - m * N4) * 4;
+    const float* part = a.part + (int64_t)m * a.ldp + n;
+    f32x4 acc = {0, 0, 0, 0};
+#pragma unroll 4
+    for (int y = 0; y < a.ksplit; ++y) acc += *reinterpret_cast<const f32x4*>(part + y * step);
     if constexpr (EPI == EPI_DH) {
       const int64_t row = a.idx[a.c0 + m];
       if (a.rs && *a.rs_off == 0) acc *= a.rs[m];
-      store_elem(reinterpret_cast<T*>(a.out) + row * a.ldo + n, acc);
+      store4(reinterpret_cast<T*>(a.out) + row * a.ldo + n, acc);
     } else {
-      float* p = a.dw + m * a.ldo + n;
-      *p = add ? *p + acc : acc;
+      float* p = a.dw + (int64_t)m * a.ldo + n;  // aligned to its elements only
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p[r] = add ? p[r] + acc[r] : acc[r];
     }
   }
 }
 
 inline unsigned tiles(int64_t n) { return (unsigned)((n + kTile - 1) / kTile); }
 
+// fp32: from two waves of 256 x 256 tiles on those are the quicker ones (16,384 rows, d = 2048, V = 32,768, the
+// three GEMMs: 14.6-15.3 ms against 16.0-16.5 ms, which read the operands 2.5 times as often); below, compute
+// units would idle (4,096 rows, d = 512, V = 6,000, the whole call: 0.92 -> 0.82 ms; 32 rows, d = 256, V = 1,000: 200 -> 104 us).
+inline bool small_f32(unsigned big_tiles) { return big_tiles < 512; }
+
+// a.M x a.N outputs (dhidden: of at most rows a.Mc)
 template <typename T, int EPI>
-hipError_t grad_impl(const GemmArgs& a, unsigned ntiles, hipStream_t s) {
-  const unsigned ny = a.ksplit > 1 ? (unsigned)a.ksplit : 1u;
-  if constexpr (EPI == EPI_DH && sizeof(T) == 2) {
-    if (a.b_kmajor) k_gemm<T, EPI, false, false, true><<<dim3(ntiles, ny), NT, 0, s>>>(a);
-    else k_gemm<T, EPI, false, false><<<dim3(ntiles, ny), NT, 0, s>>>(a);
+hipError_t grad_impl(const GemmArgs& a, hipStream_t s) {
+  const unsigned tm = tiles(EPI == EPI_DH ? a.Mc : a.M), ny = a.ksplit > 1 ? (unsigned)a.ksplit : 1u;
+  const dim3 grid(tm * tiles(a.N), ny);
+  if constexpr (sizeof(T) == 4) {
+    if (small_f32(grid.x))
+      k_gemm_f32<EPI, false><<<dim3(tm * (unsigned)((a.N + kTileN32 - 1) / kTileN32), ny), 256, 0, s>>>(a);
+    else k_gemm<T, EPI, false, false><<<grid, NT, 0, s>>>(a);
+  } else if constexpr (EPI == EPI_DH) {
+    if (a.b_kmajor) k_gemm<T, EPI, false, false, true><<<grid, NT, 0, s>>>(a);
+    else k_gemm<T, EPI, false, false><<<grid, NT, 0, s>>>(a);
   } else {
-    k_gemm<T, EPI, false, false><<<dim3(ntiles, ny), NT, 0, s>>>(a);
+    k_gemm<T, EPI, false, false><<<grid, NT, 0, s>>>(a);
   }
   if (a.ksplit > 1) {
-    const int64_t total = (int64_t)a.M * a.N;
+    const int64_t total = (int64_t)a.M * a.N / 4;
     const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 8192);
     k_splitk_reduce<T, EPI><<<blocks, 256, 0, s>>>(a);
   }
@@ -769,8 +1022,15 @@ hipError_t grad_impl(const GemmArgs& a, unsigned ntiles, hipStream_t s) {
 
 template <typename T>
 hipError_t fwd_impl(const GemmArgs& a, bool store_q, hipStream_t s) {
-  dim3 grid(tiles(a.M) * tiles(a.Mc));
+  const dim3 grid(tiles(a.M) * tiles(a.Mc));
   const bool ktail = ((int64_t)a.K * (int64_t)sizeof(T)) % KS != 0;
+  if constexpr (sizeof(T) == 4)
+    if (small_f32(grid.x)) {
+      const dim3 small(tiles(a.M) * (unsigned)((a.Mc + kTileN32 - 1) / kTileN32));
+      if (store_q) k_gemm_f32<EPI_FWD, true><<<small, 256, 0, s>>>(a);
+      else k_gemm_f32<EPI_FWD, false><<<small, 256, 0, s>>>(a);
+      return hipGetLastError();
+    }
   if (store_q) {
     if (ktail) k_gemm<T, EPI_FWD, true, true><<<grid, NT, 0, s>>>(a);
     else k_gemm<T, EPI_FWD, true, false><<<grid, NT, 0, s>>>(a);
@@ -785,23 +1045,21 @@ hipError_t fwd_impl(const GemmArgs& a, bool store_q, hipStream_t s) {
 
 hipError_t launch_fwd_gemm(int dtype, const GemmArgs& a, bool store_q, hipStream_t s) {
   prof_mark(KK_FWD_GEMM, true, s);
-  hipError_t e = dtype == RLK_DTYPE_BF16 ? fwd_impl<bf16_t>(a, store_q, s) : fwd_impl<float>(a, store_q, s);
+  const hipError_t e = dtype == RLK_DTYPE_BF16 ? fwd_impl<bf16_t>(a, store_q, s) : fwd_impl<float>(a, store_q, s);
   prof_mark(KK_FWD_GEMM, false, s);
   return e;
 }
 
 hipError_t launch_dh_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
-  const unsigned nt = tiles(a.Mc) * tiles(a.N);
   prof_mark(KK_DH_GEMM, true, s);
-  hipError_t e = dtype == RLK_DTYPE_BF16 ? grad_impl<bf16_t, EPI_DH>(a, nt, s) : grad_impl<float, EPI_DH>(a, nt, s);
+  const hipError_t e = dtype == RLK_DTYPE_BF16 ? grad_impl<bf16_t, EPI_DH>(a, s) : grad_impl<float, EPI_DH>(a, s);
   prof_mark(KK_DH_GEMM, false, s);
   return e;
 }
 
 hipError_t launch_dw_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
-  const unsigned nt = tiles(a.M) * tiles(a.N);
   prof_mark(KK_DW_GEMM, true, s);
-  hipError_t e = dtype == RLK_DTYPE_BF16 ? grad_impl<bf16_t, EPI_DW>(a, nt, s) : grad_impl<float, EPI_DW>(a, nt, s);
+  const hipError_t e = dtype == RLK_DTYPE_BF16 ? grad_impl<bf16_t, EPI_DW>(a, s) : grad_impl<float, EPI_DW>(a, s);
   prof_mark(KK_DW_GEMM, false, s);
   return e;
 }

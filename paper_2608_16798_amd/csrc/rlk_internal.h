@@ -22,6 +22,7 @@ struct bf16_t {
 
 // Tile geometry of the MFMA GEMMs (see k_gemm.hip).
 constexpr int kTile = 256;       // BM = BN = 256
+constexpr int kTileN32 = 64;     // BN of the fp32 GEMMs of few tiles (BM = 256)
 constexpr int kVocabTile = 256;  // vocabulary rows per forward tile = per online-LSE partial
 constexpr int kChunkAlign = 256; // chunk_rows granularity
 constexpr int kKAlign = 64;      // K padding of the chunk buffers (bf16 elements per stage)
@@ -38,19 +39,21 @@ constexpr float kRefQMax = 1e30f;
 constexpr float kRefSMin = 1e-30f;
 
 // Split-K plan of a gradient GEMM with at most mmax x n outputs and kbytes of K per row: with
-// fewer than 128 output tiles the K range is split over s workgroups per tile (each at least 4
-// slices), so the launch still fills the GPU; the fp32 partials go to a workspace buffer of
+// fewer than 128 output tiles (of tile_n columns) the K range is split over s workgroups per tile (each at
+// least 4 slices), so the launch still fills the GPU; the fp32 partials go to a workspace buffer of
 // s x (rows rounded to 256) x (n rounded to 256) and a reduction kernel adds them in split order.
+// `fill` workgroups are wanted: 512 of the bf16 tiles, whose compute unit holds one at a time, two waves of
+// them, and one per compute unit of the fp32 tiles (their slices are long, and every split costs its partials).
 struct SplitK {
   int s;        // splits (1 = none)
   int kslices;  // K slices per split
 };
-inline SplitK splitk_plan(int64_t mmax, int64_t n, int64_t kbytes) {
-  const int64_t tiles = ((mmax + kTile - 1) / kTile) * ((n + kTile - 1) / kTile);
+inline SplitK splitk_plan(int64_t mmax, int64_t n, int64_t kbytes, int64_t tile_n, int64_t fill) {
+  const int64_t tiles = ((mmax + kTile - 1) / kTile) * ((n + tile_n - 1) / tile_n);
   const int64_t nk = (kbytes + kGemmSliceBytes - 1) / kGemmSliceBytes;
   SplitK p = {1, (int)(nk > 0 ? nk : 1)};
   if (tiles <= 0 || tiles >= 128) return p;
-  int64_t s = 512 / tiles;
+  int64_t s = fill / tiles;
   if (s > nk / 4) s = nk / 4;
   if (s > 64) s = 64;
   if (s < 2) return p;

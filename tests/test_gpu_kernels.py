@@ -41,6 +41,19 @@ def test_gemm_tile_edges(dtype, tokens, d, V, entropy):
     compare_full(inst, run_gpu(inst, p), run_oracle(inst, p), p, tag="edges")
 
 
+
+# fp32 tiles are 256 x 64: token, feature and vocabulary edges of them; K split over many, few and no workgroups
+@pytest.mark.parametrize("tokens,d,V", [(2, 8, 1), (63, 64, 256), (64, 72, 512), (65, 56, 257), (1030, 264, 4100), (4200, 520, 8300)])
+@pytest.mark.parametrize("entropy,accumulate", [(0.0, False), (1e-2, True)])
+def test_fp32_gemm_tile_edges(tokens, d, V, entropy, accumulate):
+    ensure_library()
+    cfg, st = _all_policy("f32", tokens, d, V)
+    inst = build_instance(cfg, structure=st)
+    p = params_for(cfg, entropy_coef=entropy, accumulate_dW=accumulate)
+    dW = torch.zeros(V * d + 1, device="cuda")[1:].view(V, d)  # aligned to its elements only
+    compare_full(inst, run_gpu(inst, p, dW=dW), run_oracle(inst, p), p, tag="fp32")
+
+
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_dw_aligned_to_its_elements_only(accumulate):
     """dW may start at any fp32 element: the wide stores of the dW GEMM are not taken there.  The same
