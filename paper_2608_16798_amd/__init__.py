@@ -578,30 +578,51 @@ def value_head_bwd(hidden, w_v, mask, cu_seqlens, group_ids, dvalues, dhidden=No
     return dhidden, dw_v, db_v
 
 
+def _token_array(tokens):
+    """A call's tokens as int32.  Integer arrays and lists of plain ints are converted as a whole (0.5 million
+    tokens, the whole packing: arrays 58.7 -> 0.42 ms; lists on a slower host 112 -> 31 ms); anything else token by token, as int() takes it."""
+    import numpy as np
+
+    a = tokens
+    if isinstance(a, (list, tuple)) and len(a) and type(a[0]) is int:
+        try:
+            a = np.array(a)
+        except (ValueError, TypeError, RuntimeError):
+            pass
+    if not (isinstance(a, np.ndarray) and a.ndim == 1 and a.dtype.kind in "iu"):
+        return np.asarray([int(t) for t in tokens], np.int32)
+    if a.dtype != np.int32 and a.size and (a.min() < -2 ** 31 or a.max() >= 2 ** 31):
+        raise OverflowError("token out of bounds for int32")
+    return a.astype(np.int32, copy=False)
+
+
 def _calls_struct(calls_per_rollout):
     """Flat host arrays (kept alive in the returned tuple) and the rlk_calls_t describing them."""
     import numpy as np
 
-    call_off, x_off, y_off, xs, ys = [0], [0], [0], [], []
+    call_off, xs, ys = [0], [], []
     for calls in calls_per_rollout:
         for x, y in calls:
-            xs.extend(int(t) for t in x)
-            ys.extend(int(t) for t in y)
-            x_off.append(len(xs))
-            y_off.append(len(ys))
-        call_off.append(len(x_off) - 1)
-    arrs = dict(call_off=np.asarray(call_off, np.int64), x_off=np.asarray(x_off, np.int64),
-                y_off=np.asarray(y_off, np.int64), x_tok=np.asarray(xs, np.int32), y_tok=np.asarray(ys, np.int32))
+            xs.append(_token_array(x))
+            ys.append(_token_array(y))
+        call_off.append(len(xs))
+    off = lambda parts: np.cumsum([0] + [p.size for p in parts], dtype=np.int64)
+    flat = lambda parts: np.concatenate(parts) if parts else np.empty(0, np.int32)
+    arrs = dict(call_off=np.asarray(call_off, np.int64), x_off=off(xs), y_off=off(ys), x_tok=flat(xs), y_tok=flat(ys))
     c = Calls(R=len(calls_per_rollout), **{k: v.ctypes.data for k, v in arrs.items()})
     return c, arrs
+
+
+def _tree_sizes(c):
+    o = TreeOut()
+    _check(load_library().rlk_tree_pack(ctypes.byref(c), ctypes.byref(o)))
+    return o.n_pos, o.n_rows
 
 
 def tree_pack_sizes(calls_per_rollout):
     """(packed positions, training rows) that tree_pack will produce."""
     c, keep = _calls_struct(calls_per_rollout)
-    o = TreeOut()
-    _check(load_library().rlk_tree_pack(ctypes.byref(c), ctypes.byref(o)))
-    return o.n_pos, o.n_rows
+    return _tree_sizes(c)
 
 
 def tree_pack(calls_per_rollout, cap_pos=None, cap_rows=None) -> dict:
@@ -609,7 +630,8 @@ def tree_pack(calls_per_rollout, cap_pos=None, cap_rows=None) -> dict:
     list over rollouts of lists of (context tokens, response tokens).  Host numpy arrays."""
     import numpy as np
 
-    n_pos, n_rows = tree_pack_sizes(calls_per_rollout)
+    c, keep = _calls_struct(calls_per_rollout)
+    n_pos, n_rows = _tree_sizes(c)
     cap_pos = n_pos if cap_pos is None else cap_pos
     cap_rows = n_rows if cap_rows is None else cap_rows
     R = len(calls_per_rollout)
@@ -618,7 +640,6 @@ def tree_pack(calls_per_rollout, cap_pos=None, cap_rows=None) -> dict:
                row_src=np.zeros(max(cap_rows, 1), np.int32), row_target=np.zeros(max(cap_rows, 1), np.int32),
                row_mask=np.zeros(max(cap_rows, 1), np.uint8), row_cu=np.zeros(R + 1, np.int32),
                leaves=np.zeros(max(R, 1), np.int32))
-    c, keep = _calls_struct(calls_per_rollout)
     o = TreeOut(cap_pos=cap_pos, cap_rows=cap_rows, **{k: v.ctypes.data for k, v in out.items()})
     _check(load_library().rlk_tree_pack(ctypes.byref(c), ctypes.byref(o)))
     for k in ("token", "parent", "depth"):

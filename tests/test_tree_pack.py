@@ -135,3 +135,27 @@ def test_library_tree_pack_capacity_and_sizes():
     assert (n_pos, n_rows) == (7, 6)
     with pytest.raises(rlk.RlkError):
         rlk.tree_pack(calls, cap_pos=6)
+
+
+@pytest.mark.parametrize("form", [list, tuple, lambda t: np.asarray(t, np.int32), lambda t: np.asarray(t, np.int64),
+                                  lambda t: np.asarray(t, np.uint16), lambda t: np.repeat(np.asarray(t, np.int32), 2)[::2],
+                                  lambda t: [np.int64(v) for v in t], lambda t: [float(v) for v in t],
+                                  lambda t: np.asarray(t, np.float32), lambda t: [bool(v) if v < 2 else v for v in t]])
+def test_library_tree_pack_takes_any_token_sequence(form):
+    """Whole-array conversions (integer arrays, strided ones, lists of ints) and token by token ones."""
+    import paper_2608_16798_amd as rlk
+
+    rng = np.random.default_rng(9)
+    rolls = [random_calls(rng, n_calls=6) for _ in range(4)] + [[], [([], [])], [([], [3, 1]), ([3, 1], [])]]
+    want = O.tree_pack(rolls)
+    got = rlk.tree_pack([[(form(x), form(y)) for x, y in calls] for calls in rolls])
+    for k in want:
+        np.testing.assert_array_equal(np.asarray(got[k]), want[k], err_msg=k)
+
+
+@pytest.mark.parametrize("bad", [[2 ** 31], np.asarray([-2 ** 31 - 1]), np.asarray([2 ** 31], np.uint32), [2 ** 70]])
+def test_library_tree_pack_refuses_tokens_past_int32(bad):
+    import paper_2608_16798_amd as rlk
+
+    with pytest.raises(OverflowError):
+        rlk.tree_pack([[(bad, [1])]])
