@@ -369,7 +369,9 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
   // the two of a SIMD are of different wm: while one runs its MFMAs the other does its memory step.
   //   A half tile read in phase p is safe to overwrite from the memory step of phase p + 2 on: by then
   // the wavefronts of both groups have waited for their reads (after phase p's barrier) and passed
-  // another barrier.  Half tiles are therefore copied in the order B0 A0 B1 A1, two slices ahead, one
+  // another barrier.  (The first read, of B0 of slice 0, is waited for at once: the copy of slice 2 into
+  // that half tile follows the group of wm = 1's second barrier, its first wait of the loop comes after it.)
+  // Half tiles are therefore copied in the order B0 A0 B1 A1, two slices ahead, one
   // per phase, and every copy has five phases (1.25 slices) to land: with two copies per half tile, the
   // wait leaves 10 in flight.  B0 of the next slice is read in the last phase of a slice, so the phases
   // read 8, 4, 8 and 4 fragments.
@@ -405,6 +407,7 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
   wait_vmcnt<IN_FLIGHT>();
   block_barrier();
   step_b(c0, c0, c1, c1, 1);
+  wait_lgkm0();
   block_barrier();
   if (wm == 1) block_barrier();
   auto slice = [&](int kt, auto BUF) {
