@@ -164,14 +164,14 @@ __device__ __forceinline__ bool map_tile(int tm, int tn, int& tile_m, int& tile_
 
 // The memory step of a K-major operand: fragments f[i][kk] of its 16-row blocks by transposing reads
 // (block i's two K steps at LDS address u[i] + AT), the two copies of one of its half tiles (range rs,
-// vector offsets o, scalar offsets so, LDS destinations dst), and the step's waits.  One statement: the
+// vector offsets o, LDS destinations dst), and the step's waits.  One statement: the
 // compiler would wait for every copy in flight before each transposing read of its own (it takes the
 // read to alias the copies' LDS writes).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"  // m0 is set before each copy, here and by the compiler
 template <int AT, int VM>
 __device__ __forceinline__ void kmajor_step(const int (&u)[NB], u32x4 (&f)[NB][2], u32x4 rs, const uint32_t (&o)[2],
-                                            uint32_t so0, uint32_t so1, int dst0, int dst1) {
+                                            int dst0, int dst1) {
   static_assert(AT + 36 * 256 < 65536, "offset field");
   static_assert(NB == 2, "operand list");
   u32x2 l[NB][2], h[NB][2];
@@ -180,13 +180,13 @@ __device__ __forceinline__ void kmajor_step(const int (&u)[NB], u32x4 (&f)[NB][2
       "ds_read_b64_tr_b16 %2, %9 offset:%10\n\tds_read_b64_tr_b16 %3, %9 offset:%11\n\t"
       "ds_read_b64_tr_b16 %4, %8 offset:%12\n\tds_read_b64_tr_b16 %5, %8 offset:%13\n\t"
       "ds_read_b64_tr_b16 %6, %9 offset:%12\n\tds_read_b64_tr_b16 %7, %9 offset:%13\n\t"
-      "s_mov_b32 m0, %19\n\ts_nop 0\n\tbuffer_load_dwordx4 %15, %14, %17 offen lds\n\t"
-      "s_mov_b32 m0, %20\n\ts_nop 0\n\tbuffer_load_dwordx4 %16, %14, %18 offen lds\n\t"
-      "s_waitcnt vmcnt(%21) lgkmcnt(0)"
+      "s_mov_b32 m0, %17\n\ts_nop 0\n\tbuffer_load_dwordx4 %15, %14, 0 offen lds\n\t"
+      "s_mov_b32 m0, %18\n\ts_nop 0\n\tbuffer_load_dwordx4 %16, %14, 0 offen lds\n\t"
+      "s_waitcnt vmcnt(%19) lgkmcnt(0)"
       : "=&v"(l[0][0]), "=&v"(h[0][0]), "=&v"(l[1][0]), "=&v"(h[1][0]), "=&v"(l[0][1]), "=&v"(h[0][1]),
         "=&v"(l[1][1]), "=&v"(h[1][1])
       : "v"(u[0]), "v"(u[1]), "i"(AT), "i"(AT + 4 * 256), "i"(AT + 32 * 256), "i"(AT + 36 * 256), "s"(rs), "v"(o[0]),
-        "v"(o[1]), "s"(so0), "s"(so1), "s"(dst0), "s"(dst1), "i"(VM)
+        "v"(o[1]), "s"(dst0), "s"(dst1), "i"(VM)
       : "memory", "m0");
 #pragma unroll
   for (int i = 0; i < NB; ++i)
@@ -261,7 +261,9 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
   // the read stays inside the panel whether or not the hardware adds the scalar offset to the check.
   //   A K-major half tile is KSE K rows of 128 elements (256 bytes): an instruction moves four rows, lane
   // l the 16-byte chunk (l % 16) ^ 2 kswz(row) of row l / 16.  Chunks past the operand's last column are
-  // put out of range in the same way, K rows past the last one by the size of the slice's range.
+  // put out of range in the same way.  Every wavefront's range starts at the first of the slice's K rows that
+  // it copies and ends with the last K row, and the vector offset is the whole offset, so K rows past the last
+  // one are out of range too.
   uint32_t vo_a[2][IPH], vo_b[2][IPH];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
@@ -272,21 +274,22 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
       vo_a[h][j] = h * HALF + row < rows_a ? (uint32_t)(lane / CPR) * lda_b + chunk * 16 : 0x80000000u;
       if constexpr (KM_B) {
         const uint32_t col = h * 2 * HALF + ((lane & 15) ^ (2 * kswz((wid * IPH + j) * 4 + lane / 16))) * 16;
-        vo_b[h][j] = col < size_b ? (uint32_t)(lane / 16) * ldb_b + col : 0x80000000u;
+        vo_b[h][j] = col < size_b ? (uint32_t)(j * 4 + lane / 16) * ldb_b + col : 0x80000000u;
       } else {
         vo_b[h][j] = h * HALF + row < rows_b ? (uint32_t)(lane / CPR) * ldb_b + chunk * 16 : 0x80000000u;
       }
     }
-  // Range of slice kt of a K-major B: its K rows of [0, a.V) in this split
+  // Range of this wavefront's copies of slice kt of a K-major B: its K rows of [0, a.V) in this split
+  constexpr int KROWS = IPH * 4;  // K rows of them
   auto kmajor_range = [&](int kt) {
-    const int left = min(a.V, (ks0 + nk) * KSE) - (kt + ks0) * KSE;
-    const uint64_t base = reinterpret_cast<uint64_t>(pb) + (uint64_t)(kt + ks0) * (KSE * (uint64_t)ldb_b);
+    const int row = (kt + ks0) * KSE + wid * KROWS, left = min(a.V, (ks0 + nk) * KSE) - row;
+    const uint64_t base = reinterpret_cast<uint64_t>(pb) + (uint64_t)row * (uint64_t)ldb_b;
     return u32x4{(uint32_t)base, (uint32_t)(base >> 32) & 0xffffu,
-                 left > 0 ? (uint32_t)(min(left, KSE) - 1) * ldb_b + size_b : 0u, (uint32_t)kBufferFlags};
+                 left > 0 ? (uint32_t)(min(left, KROWS) - 1) * ldb_b + size_b : 0u, (uint32_t)kBufferFlags};
   };
   // this wavefront's copies of half h of one operand of slice kt into buffer kt % 2.  Slices past the
-  // last one are copied from an empty panel (zeros, no memory access), which keeps the number of
-  // copies in flight the same to the end of the loop.
+  // last one are copied from an empty panel (zeros, no memory access: every vector offset is out of range),
+  // which keeps the number of copies in flight the same to the end of the loop.
   auto copy_half = [&](bool op_b, int h, int kt, int buf) {
     const uint32_t kb = (uint32_t)(kt + ks0) * KS;
     const bool km = KM_B && op_b;
@@ -309,8 +312,7 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
       }
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rs, LDSP(smem + (op_b ? OPND_B : 0) + (buf * 2 + h) * HALF_B + (wid * IPH + j) * 1024), 16, o,
-          km ? (uint32_t)((wid * IPH + j) * 4) * ldb_b
-             : kb + (uint32_t)(h * HALF + (wid * IPH + j) * RPI) * (op_b ? ldb_b : lda_b), 0, 0);
+          km ? 0u : kb + (uint32_t)(h * HALF + (wid * IPH + j) * RPI) * (op_b ? ldb_b : lda_b), 0, 0);
     }
   };
   // Fragment reads: lane (lr, lg) takes logical K chunk 4 kk + lg of row lr of each 16-row block.
@@ -387,9 +389,7 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
     constexpr int rb = decltype(RB)::value, h = decltype(RH)::value, cb = decltype(CB)::value, ch = decltype(CH)::value;
     if constexpr (KM_B) {
       const int dst = (int)(uintptr_t)LDSP(smem) + OPND_B + (cb * 2 + ch) * HALF_B + wid * IPH * 1024;
-      const uint32_t so = (uint32_t)(wid * IPH * 4) * ldb_b;
-      kmajor_step<(rb * 2 + h) * HALF_B, IN_FLIGHT>(ku_b, fb[h], kmajor_range(kt), vo_b[ch], so, so + 4 * ldb_b, dst,
-                                                    dst + 1024);
+      kmajor_step<(rb * 2 + h) * HALF_B, IN_FLIGHT>(ku_b, fb[h], kmajor_range(kt), vo_b[ch], dst, dst + 1024);
     } else {
       read_b(rb, h);
       copy_half(true, ch, kt, cb);

@@ -42,6 +42,26 @@ def test_gemm_tile_edges(dtype, tokens, d, V, entropy):
 
 
 
+# W as the head of a larger allocation: what lies behind its last row must not reach any output.  The
+# probabilities of vocabulary rows past V are zero, so only NaN there shows a read (0 x NaN), in the K-major
+# dhidden GEMM (bf16) above all, whose last K slice holds 1, 63 and 1 rows of W here, or all 64
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [1, 63, 65, 256, 257, 320, 321])
+def test_rows_behind_w_are_not_read(dtype, V):
+    ensure_library()
+    cfg, st = _all_policy(dtype, 100, 136, V)
+    inst = build_instance(cfg, structure=st)
+    p = params_for(cfg)
+    out = []
+    for fill in (0.0, float("nan")):
+        buf = torch.full((V + 512, cfg.d), fill, dtype=inst["W"].dtype, device="cuda")
+        buf[:V] = inst["W"]
+        out.append(run_gpu(dict(inst, W=buf[:V]), p))
+    for k in ("dh", "dW", "logp", "ent"):
+        assert bool(torch.isfinite(out[1][k]).all()) and torch.equal(out[0][k], out[1][k]), k
+    assert out[0]["loss"] == out[1]["loss"]
+
+
 # fp32 tiles are 256 x 64: token, feature and vocabulary edges of them; K split over many, few and no workgroups
 @pytest.mark.parametrize("tokens,d,V", [(2, 8, 1), (63, 64, 256), (64, 72, 512), (65, 56, 257), (1030, 264, 4100), (4200, 520, 8300)])
 @pytest.mark.parametrize("entropy,accumulate", [(0.0, False), (1e-2, True)])
