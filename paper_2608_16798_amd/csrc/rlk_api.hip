@@ -300,10 +300,8 @@ rlk_status_t layout(const rlk_batch_t* b, bool bwd, int64_t chunk_rows, int64_t 
     L.zr = a.take((size_t)Mc * 4);
     L.st = a.take((size_t)Mc * 4);
     // split-K partials of the dhidden and dW GEMMs (used one after the other)
-    const bool f32 = esz == 4;
-    const int64_t tn = f32 ? kTileN32 : kTile, min_slices = f32 ? 8 : 4;
-    L.sk_dh = splitk_plan(Mc, d, L.Vp * esz, tn, min_slices);
-    L.sk_dw = splitk_plan(V, d, Mc * esz, tn, min_slices);
+    L.sk_dh = splitk_plan(Mc, d, L.Vp * esz);
+    L.sk_dw = splitk_plan(V, d, Mc * esz);
     plan_dw_tail(V, d, Mc * esz, L);
     size_t pb = std::max({splitk_bytes(Mc, d, L.sk_dh), splitk_bytes(V, d, L.sk_dw),
                           splitk_bytes(V - L.dw_m0, d, L.sk_dwt)});

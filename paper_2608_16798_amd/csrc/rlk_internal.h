@@ -39,22 +39,23 @@ constexpr float kRefQMax = 1e30f;
 constexpr float kRefSMin = 1e-30f;
 
 // Split-K plan of a gradient GEMM with at most mmax x n outputs and kbytes of K per row: with
-// fewer than 128 output tiles (of tile_n columns) the K range is split over s workgroups per tile, 512 in all
-// and each at least min_slices slices, so the launch still fills the GPU; the fp32 partials go to a workspace
-// buffer of s x (rows rounded to 256) x (n rounded to 256) and a reduction kernel adds them in split order.
-// The fp32 tiles take 8 slices at least, the bf16 ones 4: an fp32 slice is 16 times as long, and every split
-// costs the writing and reading of its partials.
+// fewer than 128 output tiles of 256 x 256 the K range is split over s workgroups per tile (each at least 4
+// slices), so the launch still fills the GPU; the fp32 partials go to a workspace buffer of
+// s x (rows rounded to 256) x (n rounded to 256) and a reduction kernel adds them in split order.
+// The fp32 tiles of 64 columns keep this plan: below 128 x 4 of them, two to a compute unit, a launch without
+// it does not fill the GPU either, and both the length of the fp32 sums and the row counts that share a plan
+// (whose dhidden is then bitwise the same) stay those of the 256 x 256 tiles.
 struct SplitK {
   int s;        // splits (1 = none)
   int kslices;  // K slices per split
 };
-inline SplitK splitk_plan(int64_t mmax, int64_t n, int64_t kbytes, int64_t tile_n, int64_t min_slices) {
-  const int64_t tiles = ((mmax + kTile - 1) / kTile) * ((n + tile_n - 1) / tile_n);
+inline SplitK splitk_plan(int64_t mmax, int64_t n, int64_t kbytes) {
+  const int64_t tiles = ((mmax + kTile - 1) / kTile) * ((n + kTile - 1) / kTile);
   const int64_t nk = (kbytes + kGemmSliceBytes - 1) / kGemmSliceBytes;
   SplitK p = {1, (int)(nk > 0 ? nk : 1)};
   if (tiles <= 0 || tiles >= 128) return p;
   int64_t s = 512 / tiles;
-  if (s > nk / min_slices) s = nk / min_slices;
+  if (s > nk / 4) s = nk / 4;
   if (s > 64) s = 64;
   if (s < 2) return p;
   const int64_t ks = (nk + s - 1) / s;

@@ -74,6 +74,37 @@ def test_fp32_gemm_tile_edges(tokens, d, V, entropy, accumulate):
     compare_full(inst, run_gpu(inst, p, dW=dW), run_oracle(inst, p), p, tag="fp32")
 
 
+def _bounded_call_is_the_same(dtype, tokens, d, V, outputs):
+    """Every second token trained: a call bounded by their number (half the chunk rows) against one without."""
+    ensure_library()
+    cfg, st = _all_policy(dtype, tokens, d, V)
+    mask = np.ones_like(st.mask)
+    mask[1::2] = 0
+    inst = build_instance(cfg, structure=dataclasses.replace(st, mask=mask))
+    p = params_for(cfg)
+    free, bounded = run_gpu(inst, p), run_gpu(inst, p, max_policy_tokens=(tokens + 1) // 2)
+    assert free["flags"] == bounded["flags"] == 0
+    for k in outputs:
+        assert torch.equal(free[k], bounded[k]), k
+        assert int(torch.count_nonzero(free[k])) > 0
+
+
+# dhidden of 16 and of 8 output tiles has one split plan: 32 parts of 4 K slices
+def test_fp32_dhidden_of_shapes_that_share_a_split_plan():
+    _bounded_call_is_the_same("f32", 4096, 256, 4096, ("logp", "ent", "dh"))
+
+
+# 32 output tiles (128 of 64 columns), 188 K slices in 16 parts: fp32 sums of 384 products.  The gradients are
+# 0.7e-6 off in all, 1.1e-6 and more if a sum runs over the whole vocabulary
+def test_fp32_gradient_sums_stay_short():
+    ensure_library()
+    cfg, st = _all_policy("f32", 4096, 512, 6000)
+    inst = build_instance(cfg, structure=st)
+    p = params_for(cfg)
+    m = compare_full(inst, run_gpu(inst, p), run_oracle(inst, p), p, tag="fp32 sums")
+    assert m["dh_rel"] <= 9e-7 and m["dW_rel"] <= 9e-7
+
+
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_dw_aligned_to_its_elements_only(accumulate):
     """dW may start at any fp32 element: the wide stores of the dW GEMM are not taken there.  The same
