@@ -995,10 +995,16 @@ __global__ void __launch_bounds__(256) k_splitk_reduce(GemmArgs a) {
 
 inline unsigned tiles(int64_t n) { return (unsigned)((n + kTile - 1) / kTile); }
 
-// fp32: from two waves of 256 x 256 tiles on those are the quicker ones (16,384 rows, d = 2048, V = 32,768, the
-// three GEMMs: 14.6-15.3 ms against 16.0-16.5 ms, which read the operands 2.5 times as often); below, compute
-// units would idle (4,096 rows, d = 512, V = 6,000, the whole call: 0.92 -> 0.82 ms; 32 rows, d = 256, V = 1,000: 200 -> 104 us).
-inline bool small_f32(unsigned big_tiles) { return big_tiles < 512; }
+// fp32: of many outputs 256 x 256 tiles are the quicker ones (16,384 rows, d = 2048, V = 32,768, the three GEMMs:
+// 14.2-14.7 ms against 16.1-16.6 ms of 64 columns, which read the operands 2.5 times as often); of fewer, compute
+// units idle (4,096 rows, d = 512, V = 6,000, forward and dhidden: 137 and 147 us against 115 and 143 us).  The
+// two form their sums in different orders, so for a forward and an unsplit dhidden, whose results do not depend
+// on the chunk rows, the line is drawn by the rows of the whole batch, from four waves of 256 tiles on: about two
+// of the half that is trained.  dW has its outputs fixed: two waves.
+inline bool wide_f32(const GemmArgs& a, int epi) {
+  if (epi == EPI_DW) return tiles(a.M) * tiles(a.N) >= 512;
+  return a.ksplit <= 1 && tiles(epi == EPI_FWD ? a.M : a.N) * tiles(a.rows) >= 1024;
+}
 
 // a.M x a.N outputs (dhidden: of at most rows a.Mc)
 template <typename T, int EPI>
@@ -1006,9 +1012,8 @@ hipError_t grad_impl(const GemmArgs& a, hipStream_t s) {
   const unsigned tm = tiles(EPI == EPI_DH ? a.Mc : a.M), ny = a.ksplit > 1 ? (unsigned)a.ksplit : 1u;
   const dim3 grid(tm * tiles(a.N), ny);
   if constexpr (sizeof(T) == 4) {
-    if (small_f32(grid.x))
-      k_gemm_f32<EPI, false><<<dim3(tm * (unsigned)((a.N + kTileN32 - 1) / kTileN32), ny), 256, 0, s>>>(a);
-    else k_gemm<T, EPI, false, false><<<grid, NT, 0, s>>>(a);
+    if (wide_f32(a, EPI)) k_gemm<T, EPI, false, false><<<grid, NT, 0, s>>>(a);
+    else k_gemm_f32<EPI, false><<<dim3(tm * (unsigned)((a.N + kTileN32 - 1) / kTileN32), ny), 256, 0, s>>>(a);
   } else if constexpr (EPI == EPI_DH) {
     if (a.b_kmajor) k_gemm<T, EPI, false, false, true><<<grid, NT, 0, s>>>(a);
     else k_gemm<T, EPI, false, false><<<grid, NT, 0, s>>>(a);
@@ -1028,7 +1033,7 @@ hipError_t fwd_impl(const GemmArgs& a, bool store_q, hipStream_t s) {
   const dim3 grid(tiles(a.M) * tiles(a.Mc));
   const bool ktail = ((int64_t)a.K * (int64_t)sizeof(T)) % KS != 0;
   if constexpr (sizeof(T) == 4)
-    if (small_f32(grid.x)) {
+    if (!wide_f32(a, EPI_FWD)) {
       const dim3 small(tiles(a.M) * (unsigned)((a.Mc + kTileN32 - 1) / kTileN32));
       if (store_q) k_gemm_f32<EPI_FWD, true><<<small, 256, 0, s>>>(a);
       else k_gemm_f32<EPI_FWD, false><<<small, 256, 0, s>>>(a);

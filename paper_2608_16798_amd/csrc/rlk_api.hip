@@ -556,6 +556,7 @@ rlk_status_t rlk_logprob_fwd(const rlk_batch_t* b, const void* hidden, const voi
     g.hdr = hdr;
     g.c0 = c0;
     g.Mc = L.Mc;
+    g.rows = N;
     g.ytgt = reinterpret_cast<const int32_t*>(w + L.ytgt);
     g.zy = reinterpret_cast<float*>(w + L.zy);
     g.pm = reinterpret_cast<float*>(w + L.pm);
@@ -728,6 +729,7 @@ rlk_status_t rlk_pg_loss_fwd_bwd(const rlk_batch_t* b, const void* hidden, const
     g.hdr = hdr;
     g.c0 = c0;
     g.Mc = Mcc;
+    g.rows = N;
     g.ytgt = I(L.ytgt);
     g.zy = F(L.zy);
     g.pm = F(L.pm);
@@ -830,6 +832,7 @@ rlk_status_t rlk_pg_loss_fwd_bwd(const rlk_batch_t* b, const void* hidden, const
     h.hdr = hdr;
     h.c0 = c0;
     h.Mc = Mcc;
+    h.rows = N;
     h.out = dhidden;
     h.idx = I(L.idx);
     h.ldo = b->d;

@@ -279,6 +279,7 @@ struct GemmArgs {
   const WsHeader* hdr;   // n_eff
   int64_t c0;            // first compacted row of the chunk
   int64_t Mc;            // chunk capacity
+  int64_t rows;          // forward, dhidden: rows of the whole batch
   // forward epilogue
   const int32_t* ytgt;   // compacted targets
   float* zy;

@@ -94,6 +94,14 @@ def test_fp32_dhidden_of_shapes_that_share_a_split_plan():
     _bounded_call_is_the_same("f32", 4096, 256, 4096, ("logp", "ent", "dh"))
 
 
+# Forward and unsplit dhidden take 256 x 256 tiles or such of 64 columns by the rows of the batch: 528 tiles of the
+# forward (264 of the trained rows) and 1,040 (520), 512 of dhidden (256)
+@pytest.mark.parametrize("tokens,d,V,outputs", [(4096, 264, 8448, ("logp", "ent")), (4096, 264, 16640, ("logp", "ent")),
+                                                (16384, 2048, 300, ("logp", "ent", "dh"))])
+def test_fp32_tile_width_does_not_follow_the_bound(tokens, d, V, outputs):
+    _bounded_call_is_the_same("f32", tokens, d, V, outputs)
+
+
 # 32 output tiles (128 of 64 columns), 188 K slices in 16 parts: fp32 sums of 384 products.  The gradients are
 # 0.7e-6 off in all, 1.1e-6 and more if a sum runs over the whole vocabulary
 def test_fp32_gradient_sums_stay_short():
