@@ -212,13 +212,14 @@ __global__ void __launch_bounds__(256) k_hidden_t(const uint16_t* hc, int d, con
 }
 
 // ---- merge of the per-vocabulary-tile partials (m, s, u) into lse, logp, H; loss scalars.
-// A block of 16 wavefronts merges TOK tokens: a wavefront holds 64 / TOK strides of vocabulary tiles, and a
-// lane merges the tiles k = stride, stride + G, ... (G = 16 * 64 / TOK) of its token, kBatch tiles' loads in
-// flight, with a running maximum M:
+// A block of 16 wavefronts merges TOK tokens.  The vocabulary tiles are dealt to G = 64 strides k, k + G, ...,
+// four to a wavefront; a lane merges one stride of its token (TOK = 16) or its wavefront's four (TOK = 64), four
+// or eight tiles' loads in flight, kBatch tiles at a time with a running maximum M:
 //   S = sum_k e^{m_k - M} s_k,  T = sum_k e^{m_k - M} (u_k + (m_k - M) s_k),
 // rescaled by e^{M - M'} (and T shifted by (M - M') S) whenever a batch raises the maximum to M'; the
-// strides meet by shuffles, then in LDS, the same way.  Then lse = M + ln S and
-// sum_j p_j (z_j - lse) = T / S - ln S.
+// strides meet by shuffles or in registers, then in LDS, the same way.  Then lse = M + ln S and
+// sum_j p_j (z_j - lse) = T / S - ln S.  The order of the sums is the same for either TOK: a token's results
+// do not depend on the chunk rows.
 // Bound by the latency of the loads: few tokens are dealt in blocks of 16, with 64 strides of tiles side by
 // side, many in blocks of 64, whose loads are whole lines.  Against blocks of 64 tokens on four wavefronts, one
 // tile in flight: 160 tokens of 594 tiles 107 -> 9 us, 770 tokens 127 -> 14 us, 23,000 tokens of 196 tiles 52 -> 20 us.
@@ -230,15 +231,18 @@ __device__ __forceinline__ void merge_partial(float& M, double& S, double& T, fl
   const float n = fmaxf(M, m);
   const float da = M == -INFINITY ? 0.0f : M - n, db = m == -INFINITY ? 0.0f : m - n;
   const double fa = (double)__builtin_amdgcn_exp2f(da * kLog2e), fb = (double)__builtin_amdgcn_exp2f(db * kLog2e);
-  T = fa * (T + (double)da * S) + fb * (t + (double)db * s);
-  S = fa * S + fb * s;
+  T = fma(fa, fma((double)da, S, T), fb * fma((double)db, s, t));
+  S = fma(fa, S, fb * s);
   M = n;
 }
 
 template <int TOK>
 __global__ void __launch_bounds__(64 * kCombineWaves) k_combine(TokenParams p) {
-  constexpr int kBatch = 4;
-  constexpr int SUB = 64 / TOK, G = SUB * kCombineWaves;
+  constexpr int kBatch = 2;
+  constexpr int SUB = 4, G = SUB * kCombineWaves;  // strides of a wavefront, of a block
+  constexpr int OWN = SUB * TOK / 64;              // of them, a lane's
+  constexpr int LOADS = OWN == 1 ? 4 : 2;          // tiles of a stride in flight
+  static_assert(OWN == 1 || OWN == SUB, "one stride or all");
   __shared__ float s_m[kCombineWaves][TOK];
   __shared__ double s_S[kCombineWaves][TOK], s_T[kCombineWaves][TOK];
   int64_t rc = (int64_t)p.hdr->n_eff - p.c0;
@@ -248,44 +252,64 @@ __global__ void __launch_bounds__(64 * kCombineWaves) k_combine(TokenParams p) {
   const int tok = lane % TOK;
   const int64_t tl = (int64_t)blockIdx.x * TOK + tok;
   const bool act = tl < rc;
-  float M = -INFINITY;
-  double S = 0.0, T = 0.0;
+  float Mo[OWN];
+  double So[OWN], To[OWN];
+#pragma unroll
+  for (int q = 0; q < OWN; ++q) {
+    Mo[q] = -INFINITY;
+    So[q] = To[q] = 0.0;
+  }
   if (act)
-    for (int k0 = wv * SUB + lane / TOK; k0 < p.nvt; k0 += kBatch * G) {
-      float mk[kBatch], sk[kBatch], uk[kBatch];
+    for (int kb = wv * SUB + (OWN == 1 ? lane / TOK : 0); kb < p.nvt; kb += LOADS * G) {
+      float mk[OWN][LOADS], sk[OWN][LOADS], uk[OWN][LOADS];
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        const int k = k0 + j * G;
-        const int64_t o = (int64_t)(k < p.nvt ? k : k0) * p.Mc + tl;
-        mk[j] = p.pm[o];
-        sk[j] = p.ps[o];
-        uk[j] = p.pu[o];
-        if (k >= p.nvt) mk[j] = -INFINITY;
-      }
-      float n = M;
+      for (int q = 0; q < OWN; ++q)
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) n = fmaxf(n, mk[j]);
-      if (n > M) {
-        if (M > -INFINITY) {
-          const double f = (double)__builtin_amdgcn_exp2f((M - n) * kLog2e);
-          T = f * (T + (double)(M - n) * S);
-          S *= f;
+        for (int j = 0; j < LOADS; ++j) {
+          const int k = kb + q + j * G;
+          const int64_t o = (int64_t)(k < p.nvt ? k : kb) * p.Mc + tl;
+          mk[q][j] = p.pm[o];
+          sk[q][j] = p.ps[o];
+          uk[q][j] = p.pu[o];
+          if (k >= p.nvt) mk[q][j] = -INFINITY;
         }
-        M = n;
-      }
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        if (k0 + j * G >= p.nvt) break;
-        const double w = (double)__builtin_amdgcn_exp2f((mk[j] - M) * kLog2e);
-        S += w * (double)sk[j];
-        T += w * ((double)uk[j] + (double)(mk[j] - M) * (double)sk[j]);
+      for (int qb = 0; qb < OWN * LOADS / kBatch; ++qb) {
+        const int q = qb / (LOADS / kBatch), j0 = qb % (LOADS / kBatch) * kBatch;
+        float n = Mo[q];
+#pragma unroll
+        for (int j = j0; j < j0 + kBatch; ++j) n = fmaxf(n, mk[q][j]);
+        if (n > Mo[q]) {
+          if (Mo[q] > -INFINITY) {
+            const double f = (double)__builtin_amdgcn_exp2f((Mo[q] - n) * kLog2e);
+            To[q] = f * fma((double)(Mo[q] - n), So[q], To[q]);
+            So[q] *= f;
+          }
+          Mo[q] = n;
+        }
+#pragma unroll
+        for (int j = j0; j < j0 + kBatch; ++j) {
+          if (kb + q + j * G >= p.nvt) break;
+          const double w = (double)__builtin_amdgcn_exp2f((mk[q][j] - Mo[q]) * kLog2e);
+          So[q] = fma(w, (double)sk[q][j], So[q]);
+          To[q] = fma(w, fma((double)(mk[q][j] - Mo[q]), (double)sk[q][j], (double)uk[q][j]), To[q]);
+        }
       }
     }
+  // strides 0 + 1, 2 + 3, then the two
+  float M = Mo[0];
+  double S = So[0], T = To[0];
+  if constexpr (OWN == 1) {
 #pragma unroll
-  for (int o = TOK; o < 64; o <<= 1) {
-    const float m = __shfl_xor(M, o, 64);
-    const double s = __shfl_xor(S, o, 64), t = __shfl_xor(T, o, 64);
-    merge_partial(M, S, T, m, s, t);
+    for (int o = TOK; o < 64; o <<= 1) {
+      const float m = __shfl_xor(M, o, 64);
+      const double s = __shfl_xor(S, o, 64), t = __shfl_xor(T, o, 64);
+      merge_partial(M, S, T, m, s, t);
+    }
+  } else {
+    merge_partial(M, S, T, Mo[1], So[1], To[1]);
+    merge_partial(Mo[2], So[2], To[2], Mo[3], So[3], To[3]);
+    merge_partial(M, S, T, Mo[2], So[2], To[2]);
   }
   if (lane < TOK) {
     s_m[wv][lane] = M;

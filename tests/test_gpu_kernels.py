@@ -94,6 +94,11 @@ def test_fp32_dhidden_of_shapes_that_share_a_split_plan():
     _bounded_call_is_the_same("f32", 4096, 256, 4096, ("logp", "ent", "dh"))
 
 
+# bf16: W^T without the bound, W itself (K-major) with it: the same products in the same order
+def test_bf16_dhidden_from_w_and_from_its_transpose_are_the_same():
+    _bounded_call_is_the_same("bf16", 16384, 136, 321, ("logp", "ent", "dh"))
+
+
 # Forward and unsplit dhidden take 256 x 256 tiles or such of 64 columns by the rows of the batch: 528 tiles of the
 # forward (264 of the trained rows) and 1,040 (520), 512 of dhidden (256)
 @pytest.mark.parametrize("tokens,d,V,outputs", [(4096, 264, 8448, ("logp", "ent")), (4096, 264, 16640, ("logp", "ent")),
@@ -251,6 +256,13 @@ def test_compaction_block_edges(N, R):
     np.testing.assert_array_equal(to_host(idx)[:n], widx)
     np.testing.assert_array_equal(to_host(tokr)[:n], wtokr)
     np.testing.assert_array_equal(to_host(n_pol), wn)
+
+
+# the merge takes blocks of 64 tokens for the 8,192 chunk rows without the bound, of 16 for the 4,096 with it
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [300, 17 * 256, 70 * 256, 330 * 256 + 1])
+def test_combine_does_not_depend_on_the_chunk_rows(dtype, V):
+    _bounded_call_is_the_same(dtype, 8192, 64, V, ("logp", "ent"))
 
 
 # the merge of the vocabulary tiles: blocks of 16 tokens up to 4,096 chunk rows and of 64 above, tiles dealt in
