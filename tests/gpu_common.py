@@ -26,6 +26,9 @@ TOL_LOSS = 1e-3
 # there the relative bound is taken against that fraction of the L1 size instead of |loss|.
 LOSS_CANCEL_FRAC = 1e-2
 TOL_GRAD = 2e-2
+# fp32 gradients: sums of up to 2^13 products in fp32 (their order's worst case aside, a relative error of
+# 2^-24 sqrt(2^13) = 5e-6), twice that for the probabilities that go into them
+TOL_GRAD_F32 = 1e-5
 
 
 def log(*a):
@@ -186,7 +189,8 @@ def compare_full(inst, gpu, ref, params, tag=""):
     assert m["logp_abs"] <= tl and m["ent_abs"] <= tl
     assert m["masked_nonzero"] == 0 and m["dh_masked_nonzero"] == 0
     assert m["loss_err"] <= TOL_LOSS
-    assert m["dh_rel"] <= TOL_GRAD and m["dW_rel"] <= TOL_GRAD
+    tg = TOL_GRAD_F32 if cfg.dtype == "f32" else TOL_GRAD
+    assert m["dh_rel"] <= tg and m["dW_rel"] <= tg
     assert m["stats_ok"]
     assert m["kl_mean_err"] <= 1e-3 and m["tis_mean_err"] <= 1e-4
     # the explicit dz pass runs for every chunk unless the token-reference layout applies (bf16

@@ -64,14 +64,25 @@ def test_rows_behind_w_are_not_read(dtype, V):
 
 # fp32 tiles are 256 x 64: token, feature and vocabulary edges of them; K split over many, few and no workgroups
 @pytest.mark.parametrize("tokens,d,V", [(2, 8, 1), (63, 64, 256), (64, 72, 512), (65, 56, 257), (1030, 264, 4100), (4200, 520, 8300)])
-@pytest.mark.parametrize("entropy,accumulate", [(0.0, False), (1e-2, True)])
-def test_fp32_gemm_tile_edges(tokens, d, V, entropy, accumulate):
+@pytest.mark.parametrize("entropy", [0.0, 1e-2])
+def test_fp32_gemm_tile_edges(tokens, d, V, entropy):
     ensure_library()
     cfg, st = _all_policy("f32", tokens, d, V)
     inst = build_instance(cfg, structure=st)
-    p = params_for(cfg, entropy_coef=entropy, accumulate_dW=accumulate)
-    dW = torch.zeros(V * d + 1, device="cuda")[1:].view(V, d)  # aligned to its elements only
-    compare_full(inst, run_gpu(inst, p, dW=dW), run_oracle(inst, p), p, tag="fp32")
+    p = params_for(cfg, entropy_coef=entropy)
+    ref = run_oracle(inst, p)
+    compare_full(inst, run_gpu(inst, p), ref, p, tag="fp32")
+    # added to a preset dW of the gradients' size, aligned to 16 bytes or to its elements only
+    pa = params_for(cfg, entropy_coef=entropy, accumulate_dW=True)
+    scale = float(np.abs(ref["dW"]).max()) or 1.0
+    preset = scale * torch.randn(V * d, generator=torch.Generator(device="cuda").manual_seed(V), device="cuda")
+    want = to_host(preset).astype(np.float64).reshape(V, d) + ref["dW"]
+    for off in (0, 1):
+        buf = torch.empty(V * d + 4, device="cuda")
+        dW = buf[off:off + V * d].copy_(preset).view(V, d)
+        run_gpu(inst, pa, dW=dW)
+        # the gradient's own error and one rounding of a sum of up to six times its size
+        assert np.abs(to_host(dW) - want).max() <= (1e-5 + 6 * 2.0 ** -24) * scale, off
 
 
 def _bounded_call_is_the_same(dtype, tokens, d, V, outputs):
