@@ -285,18 +285,21 @@ rlk_status_t layout(const rlk_batch_t* b, bool bwd, int64_t chunk_rows, int64_t 
   L.pu = a.take((size_t)L.nvt * Mc * 4);
   L.hc = a.take((size_t)(Mc * d * esz));
   if (bwd) {
-    // W^T costs one read and one write of W per call, reading W by transposing fragment reads 5 % of
-    // the dhidden GEMM (81 instead of 86 % MFMA busy).  At d = 4096, V = 151,936 that is 0.52 ms against
-    // 0.04 us per row: even at 12,000 rows, whatever d and V (both terms grow with V d).  At 770 rows
-    // the call went from 3.36 to 2.86 ms.
-    L.w_kmajor = esz == 2 && B <= 8192;
+    // W^T costs one read and one write of W per call, reading W by transposing fragment reads 1-2 % of the
+    // dhidden GEMM; both grow with V d, so the line is one of rows.  The call with W^T and without it, d = 4096,
+    // V = 151,936: 770 rows 3.36 and 2.86 ms, 8,900 rows 23.8 and 23.4 ms, 13,300 rows 35.7 and 35.3 ms, 16,200
+    // rows 43.0 and 42.7 ms; d = 2048, V = 32,768: 13,300 rows 4.17 and 4.14 ms, 16,200 rows 4.94 and 4.92 ms.
+    // The rows are the caller's bound on the trained tokens, or all tokens without one.
+    L.w_kmajor = esz == 2 && B <= 16384;
     L.ldq = pad_ld(L.Vp, esz);
     L.ldt = pad_ld(Mc, esz);
     L.ldw = pad_ld(L.Vp, esz);
     L.ht = a.take((size_t)(d * L.ldt * esz));
     L.q = a.take((size_t)(Mc * L.ldq * esz));
     L.dzt = a.take((size_t)(L.Vp * L.ldt * esz));
-    L.wt = a.take((size_t)(d * L.ldw * esz));  // reserved for every row count
+    // Reserved for every row count: with chunk_rows given, a workspace sized for one bound on the trained tokens
+    // takes a call with a larger one.
+    L.wt = a.take((size_t)(d * L.ldw * esz));
     L.zr = a.take((size_t)Mc * 4);
     L.st = a.take((size_t)Mc * 4);
     // split-K partials of the dhidden and dW GEMMs (used one after the other)

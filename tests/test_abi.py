@@ -62,6 +62,18 @@ def test_workspace_sizes(lib, name):
     assert big > bwd
 
 
+def test_workspace_of_a_bound_takes_a_larger_bound(lib):
+    """With chunk_rows given, the bound on the trained tokens does not size the workspace: one that a small
+    call sized (its dhidden GEMM reads W as it lies) takes a large one (which forms W^T there)."""
+    b = _batch(get_config("qwen8b_bf16"), N=65536)
+    p = rlk.make_params(chunk_rows=1024)
+    sizes = []
+    for bound in (1024, 9000, 16384, 16385, 40000):
+        b.max_policy_tokens = bound
+        sizes.append(rlk.workspace_size(b, p))
+    assert len(set(sizes)) == 1, sizes
+
+
 def test_host_validation(lib):
     cfg = get_config("tiny_fp32")
     n = ctypes.c_size_t()

@@ -27,11 +27,12 @@ def _all_policy(dtype, tokens, d, V):
 
 
 # K slices of the forward: 1, 2, 3 (whole and with a tail); token and vocabulary tiles one short of, at and
-# one past the tile's and its halves' edges; bf16 calls of more than 8,192 rows read W^T in the dhidden GEMM, the
+# one past the tile's and its halves' edges; bf16 calls of more than 16,384 rows read W^T in the dhidden GEMM, the
 # others W itself
 @pytest.mark.parametrize("dtype,tokens,d,V", [
     ("bf16", 2, 8, 1), ("bf16", 127, 64, 129), ("bf16", 129, 72, 255), ("bf16", 255, 128, 256), ("bf16", 256, 136, 257),
-    ("bf16", 257, 192, 513), ("bf16", 300, 520, 1), ("bf16", 8192, 136, 321), ("bf16", 8193, 136, 321), ("f32", 127, 8, 129), ("f32", 129, 32, 257), ("f32", 257, 40, 255), ("f32", 255, 96, 300)])
+    ("bf16", 257, 192, 513), ("bf16", 300, 520, 1), ("bf16", 8192, 136, 321),
+    ("bf16", 16384, 136, 321), ("bf16", 16385, 136, 321), ("f32", 127, 8, 129), ("f32", 129, 32, 257), ("f32", 257, 40, 255), ("f32", 255, 96, 300)])
 @pytest.mark.parametrize("entropy", [0.0, 1e-2])
 def test_gemm_tile_edges(dtype, tokens, d, V, entropy):
     ensure_library()
@@ -107,7 +108,7 @@ def test_fp32_dhidden_of_shapes_that_share_a_split_plan():
 
 # bf16: W^T without the bound, W itself (K-major) with it: the same products in the same order
 def test_bf16_dhidden_from_w_and_from_its_transpose_are_the_same():
-    _bounded_call_is_the_same("bf16", 16384, 136, 321, ("logp", "ent", "dh"))
+    _bounded_call_is_the_same("bf16", 32768, 136, 250, ("logp", "ent", "dh"))
 
 
 # Forward and unsplit dhidden take 256 x 256 tiles or such of 64 columns by the rows of the batch: 528 tiles of the
