@@ -231,13 +231,16 @@ def test_value_head_row_and_column_splits(dtype, lens, d, accumulate):
         assert torch.equal(dh[torch.as_tensor(on[:, 0] == 0, device="cuda")], dh0[torch.as_tensor(on[:, 0] == 0, device="cuda")])
 
 
-# one workgroup up to 1,024 rollouts; beyond, runs of 1,024 (whole, a short last one, all sixteen)
-@pytest.mark.parametrize("R,G", [(1, 1), (63, 4), (64, 64), (65, 1), (1023, 7), (1024, 1024), (1025, 3), (2048, 16),
-                                 (5000, 5000), (16384, 1), (16383, 97)])
+# one workgroup up to 1,024 rollouts, 64 to 4 lanes per group of up to 64 and a wavefront per larger one (G = 0: one
+# of half the rollouts beside groups of one); beyond, runs of 1,024 (whole, a short last one, all sixteen)
+@pytest.mark.parametrize("R,G", [(1, 1), (63, 4), (64, 64), (65, 1), (260, 1), (300, 2), (1024, 1), (1024, 64), (1024, 68),
+                                 (1024, 0), (1023, 7), (1024, 1024), (1025, 3), (2048, 16), (5000, 5000), (16384, 1),
+                                 (16383, 97)])
 def test_group_advantage_run_edges(R, G):
     ensure_library()
     rng = np.random.default_rng(R + G)
-    gid = rng.permutation(np.arange(R) // G).astype(np.int32) * 5 + 2
+    key = np.arange(R) // G if G else np.maximum(np.arange(R) - R // 2, 0)
+    gid = rng.permutation(key).astype(np.int32) * 5 + 2
     gid[rng.random(R) < 0.05] = -3
     rew = (rng.integers(0, 4, R) / 4).astype(np.float32)
     idx, count = torch.full((R,), 9, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
