@@ -172,20 +172,20 @@ k_gae(int64_t N, const int32_t* cu, const uint8_t* mask, const float* values, co
 }
 
 // ---- value loss: fp64 partial sums of (rollout, slice of its rows), their total, then the gradient.
-// A rollout's rows are cut into groups of 8 x 256 rows, dealt to kValueSplit slices, so that a batch of
+// A rollout's rows are cut into groups of 8 x THREADS rows, dealt to kValueSplit slices, so that a batch of
 // few long rollouts still fills the GPU.  128 rollouts of 1,024 to 7,168 rows: three launches of one
 // row per thread 22.7 us -> two launches 9.8 us.
-template <bool VEC>
-__global__ void __launch_bounds__(256)
+template <bool VEC, int THREADS>
+__global__ void __launch_bounds__(THREADS)
 k_value_partial(int64_t N, const int32_t* cu, const uint8_t* mask, const float* values, const float* ret,
                 const int32_t* gid, double* part) {
-  __shared__ double sh[4][2];
+  __shared__ double sh[THREADS / 64][2];
   const int r = blockIdx.x;
   const int64_t s0 = clamp64(cu[r], 0, N), s1 = clamp64(cu[r + 1], s0, N);
   double ss = 0.0, cnt = 0.0;
   if (!(gid && gid[r] < 0)) {
-    for (int64_t g = s0 / kGaeRows * kGaeRows + ((int64_t)blockIdx.y * 256 + threadIdx.x) * kGaeRows; g < s1;
-         g += (int64_t)gridDim.y * 256 * kGaeRows) {
+    for (int64_t g = s0 / kGaeRows * kGaeRows + ((int64_t)blockIdx.y * THREADS + threadIdx.x) * kGaeRows;
+         g < s1; g += (int64_t)gridDim.y * THREADS * kGaeRows) {
       float v[kGaeRows], t[kGaeRows];
       const uint32_t pol = load_rows<VEC>(g, s0, s1, N, mask, values, v);
       load_rows<VEC>(g, s0, s1, N, mask, ret, t);
@@ -207,9 +207,11 @@ k_value_partial(int64_t N, const int32_t* cu, const uint8_t* mask, const float* 
     sh[threadIdx.x >> 6][1] = cnt;
   }
   __syncthreads();
-  if (threadIdx.x < 2)
-    part[((int64_t)r * gridDim.y + blockIdx.y) * 2 + threadIdx.x] =
-        sh[0][threadIdx.x] + sh[1][threadIdx.x] + sh[2][threadIdx.x] + sh[3][threadIdx.x];
+  if (threadIdx.x < 2) {
+    double t = 0.0;
+    for (int k = 0; k < THREADS / 64; ++k) t += sh[k][threadIdx.x];
+    part[((int64_t)r * gridDim.y + blockIdx.y) * 2 + threadIdx.x] = t;
+  }
 }
 
 // total of n partials in a fixed order (the same in every block that forms it)
@@ -249,23 +251,23 @@ __global__ void __launch_bounds__(1024) k_value_final(int n, const double* part,
 
 // With npart > 0 every block adds up the partials itself (and block 0 writes the loss), which saves the
 // launch of k_value_final; otherwise the count is in total.
-template <bool VEC>
-__global__ void __launch_bounds__(256)
+template <bool VEC, int THREADS>
+__global__ void __launch_bounds__(THREADS)
 k_value_grad(int64_t N, const int32_t* cu, const uint8_t* mask, const float* values, const float* ret,
              const int32_t* gid, int npart, const double* part, const double* total, float* loss, float* dv) {
   const int r = blockIdx.x;
   double n;
   if (npart > 0) {
     double sum;
-    value_total<256>(npart, part, sum, n);
+    value_total<THREADS>(npart, part, sum, n);
     if (r == 0 && blockIdx.y == 0 && threadIdx.x == 0) loss[0] = n > 0 ? (float)(sum / n) : 0.0f;
   } else {
     n = total[0];
   }
   const int64_t s0 = clamp64(cu[r], 0, N), s1 = clamp64(cu[r + 1], s0, N);
   const bool on = !(gid && gid[r] < 0) && n > 0;
-  for (int64_t g = s0 / kGaeRows * kGaeRows + ((int64_t)blockIdx.y * 256 + threadIdx.x) * kGaeRows; g < s1;
-       g += (int64_t)gridDim.y * 256 * kGaeRows) {
+  for (int64_t g = s0 / kGaeRows * kGaeRows + ((int64_t)blockIdx.y * THREADS + threadIdx.x) * kGaeRows;
+       g < s1; g += (int64_t)gridDim.y * THREADS * kGaeRows) {
     float v[kGaeRows], t[kGaeRows], o[kGaeRows];
     const uint32_t pol = load_rows<VEC>(g, s0, s1, N, mask, values, v);
     load_rows<VEC>(g, s0, s1, N, mask, ret, t);
@@ -582,16 +584,25 @@ hipError_t launch_value_head_bwd(int dtype, int64_t N, int d, int R, const void*
   return hipGetLastError();
 }
 
+// Rollouts enough to fill the GPU with single wavefronts, and for the most part one pass of a wavefront (512 rows)
+// or less: below 1,024 of them a wavefront is no quicker (15 us of launch and latency either way).
+inline bool many_short_rollouts(int64_t N, int R) { return R > 1024 && N / R <= 256; }
+
 hipError_t launch_gae(int64_t N, int R, const int32_t* cu, const uint8_t* mask, const float* values,
                       const float* rewards, const int32_t* gid, float gamma, float lam, float* adv, float* ret,
                       hipStream_t s) {
-  // Long rollouts get a workgroup that covers 8,192 rows in one pass; short ones leave its barriers and
-  // wavefronts idle and get the small one (the mean length decides; either is right for any length).
+  // Up to two workgroups of 1,024 threads per compute unit, long rollouts get one each, which covers 8,192 rows in
+  // one pass; more of them fill the GPU with smaller ones, and the large ones would wait for each other
+  // (16,384 rollouts of 2,000 rows: 437 us, with 256 threads 131 us; 2,048: 22 us with 256, 1,024 30 us with
+  // 1,024 threads).  Many short ones get a wavefront (16,384 of 61 rows: 62 us with 256 threads, 19 us with 64).
+  // The mean length decides; each is right for any length.
   prof_mark(KK_GAE, true, s);
   const bool vec = aligned16(mask) && aligned16(values) && aligned16(adv) && aligned16(ret);
-  const bool big = N / R > 1024;
-  auto* k = big ? (vec ? k_gae<true, 1024> : k_gae<false, 1024>) : (vec ? k_gae<true, 256> : k_gae<false, 256>);
-  k<<<R, big ? 1024 : 256, 0, s>>>(N, cu, mask, values, rewards, gid, gamma, lam, adv, ret);
+  const int threads = many_short_rollouts(N, R) ? 64 : (R <= 512 && N / R > 1024 ? 1024 : 256);
+  auto* k = threads == 1024 ? (vec ? k_gae<true, 1024> : k_gae<false, 1024>)
+            : threads == 256 ? (vec ? k_gae<true, 256> : k_gae<false, 256>)
+                             : (vec ? k_gae<true, 64> : k_gae<false, 64>);
+  k<<<R, threads, 0, s>>>(N, cu, mask, values, rewards, gid, gamma, lam, adv, ret);
   prof_mark(KK_GAE, false, s);
   return hipGetLastError();
 }
@@ -605,13 +616,18 @@ hipError_t launch_value_loss(int64_t N, int R, const int32_t* cu, const uint8_t*
   const int ny = (int)std::min<int64_t>(std::max<int64_t>(R > 0 ? N / R / 2048 : 1, 1), kValueSplit);
   const dim3 grid(R, ny);
   const int np = R * ny;
-  (vec ? k_value_partial<true> : k_value_partial<false>)<<<grid, 256, 0, s>>>(N, cu, mask, values, ret, gid, part);
+  const bool small = many_short_rollouts(N, R);  // a wavefront each (16,384 of 61 rows: 44 -> 29 us)
+  const unsigned threads = small ? 64 : 256;
+  (small ? (vec ? k_value_partial<true, 64> : k_value_partial<false, 64>)
+         : (vec ? k_value_partial<true, 256> : k_value_partial<false, 256>))<<<grid, threads, 0, s>>>(N, cu, mask, values,
+                                                                                                  ret, gid, part);
   // up to 1,024 partials the gradient's blocks add them up themselves (four loads per thread)
   const bool own_total = dv && np <= 1024;
   if (!own_total) k_value_final<<<1, 1024, 0, s>>>(np, part, total, loss);
   if (dv)
-    (vec ? k_value_grad<true> : k_value_grad<false>)<<<grid, 256, 0, s>>>(N, cu, mask, values, ret, gid, own_total ? np : 0,
-                                                                          part, total, loss, dv);
+    (small ? (vec ? k_value_grad<true, 64> : k_value_grad<false, 64>)
+           : (vec ? k_value_grad<true, 256> : k_value_grad<false, 256>))<<<grid, threads, 0, s>>>(
+        N, cu, mask, values, ret, gid, own_total ? np : 0, part, total, loss, dv);
   prof_mark(KK_VALUE_LOSS, false, s);
   return hipGetLastError();
 }

@@ -196,6 +196,35 @@ def test_value_loss_of_many_rollouts():
     np.testing.assert_allclose(to_host(dv), rdv, rtol=0, atol=2e-7 * np.abs(rdv).max())
 
 
+# more than 1,024 rollouts: a wavefront per rollout up to a mean length of 256 (single ones take several passes), a
+# workgroup of four beyond
+@pytest.mark.parametrize("R,mean", [(1025, 6), (1030, 256), (1030, 260)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_gae_and_value_loss_of_many_rollouts(R, mean, off):
+    ensure_library()
+    rng = np.random.default_rng(R + mean)
+    lens = rng.integers(0, mean, R)
+    lens[3], lens[R - 1] = 513, 1100
+    lens[5] += max(0, R * mean - int(lens.sum()))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    N = int(cu[-1])
+    mask = (rng.random(N) < 0.5).astype(np.uint8)
+    vals, rets, rew = (rng.standard_normal(n).astype(np.float32) for n in (N, N, R))
+
+    def dev(a):
+        return torch.as_tensor(np.concatenate([a[:off], a]), device="cuda")[off:]
+
+    v, t, m, c = dev(vals), dev(rets), dev(mask), torch.as_tensor(cu, device="cuda")
+    loss, dv = rlk.value_loss(v, t, m, c)
+    rl, rdv = O.value_loss(vals, rets, mask, cu)
+    assert abs(float(loss.item()) - rl) <= 2e-7 * abs(rl)
+    np.testing.assert_allclose(to_host(dv), rdv, rtol=0, atol=2e-7 * np.abs(rdv).max())
+    adv, ret = rlk.gae(v, torch.as_tensor(rew, device="cuda"), m, c, torch.zeros(R, dtype=torch.int32, device="cuda"), 0.99, 0.95)
+    ra, rr = O.gae(vals, rew, mask, cu, np.zeros(R, np.int32), float(np.float32(0.99)), float(np.float32(0.95)))
+    np.testing.assert_allclose(to_host(adv), ra, rtol=0, atol=2e-7 * np.abs(ra).max())
+    np.testing.assert_allclose(to_host(ret), rr, rtol=0, atol=2e-7 * np.abs(rr).max())
+
+
 # rows of fewer than 256 16-byte chunks are dealt among the threads (8 features: 256 rows side by side; 1,360:
 # one row and a rest of idle threads), wider ones take several passes; 128 rows per workgroup
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
