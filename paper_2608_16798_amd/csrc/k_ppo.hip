@@ -343,15 +343,16 @@ __device__ __forceinline__ int list_kept(int64_t t0, int64_t N, const uint8_t* m
   return n;
 }
 
-// Forward: HBM bound (one read of the kept rows), one wavefront per row, eight loads in flight per lane:
+// Forward: HBM bound (one read of the kept rows), one wavefront per row, BATCH 16-byte loads in flight per lane (8,
+// or for rows of one load per lane 1: 300,000 rows of 64 bf16, all kept, 79 us with
+// the batch, 75 us without):
 // 131,072 rows of 4,096 bf16, 40 % kept, after a pass that writes 1 GB: 132 us without the batch, 122 us
 // with it (3.5 TB/s).  Listing the kept rows of 32 first, so that no wavefront starts for the others, took 158 us.
-template <typename T>
+template <typename T, int BATCH>
 __global__ void __launch_bounds__(256)
 k_value_head_fwd(int64_t N, int d, const T* h, const T* w, float b, const uint8_t* mask, const int32_t* cu,
                  const int32_t* gid, int R, float* values) {
   constexpr int EPC = 16 / sizeof(T);
-  constexpr int BATCH = 8;  // 16-byte loads in flight per lane
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (t >= N) return;
@@ -393,7 +394,7 @@ k_value_head_fwd(int64_t N, int d, const T* h, const T* w, float b, const uint8_
 template <typename T>
 __global__ void __launch_bounds__(512)
 k_value_head_bwd(int64_t N, int d, const T* h, const T* w, const float* dv, const uint8_t* mask, const int32_t* cu,
-                 const int32_t* gid, int R, T* dh, int accumulate, float* part, double* part_db) {
+                 const int32_t* gid, int R, T* dh, int accumulate, int window, float* part, double* part_db) {
   constexpr int EPC = 16 / sizeof(T);
   constexpr int BATCH = 8;  // rows in flight per thread
   __shared__ int16_t list[kHeadRows];
@@ -416,12 +417,17 @@ k_value_head_bwd(int64_t N, int d, const T* h, const T* w, const float* dv, cons
     if ((i & 63) == 0) db_s[i >> 6] = s;
   }
   __syncthreads();
-  const int nch = d / EPC;
+  const int w0 = blockIdx.y * window, nch = min(window, d / EPC - w0);  // the workgroup's 16-byte chunks of a row
   const int deal = nch >= 256 ? 1 : 256 / nch;  // rows side by side
   const int ti = i & 255;
   const int c0 = deal == 1 ? ti : ti % nch, sub = deal == 1 ? 0 : ti / nch;
+  // from here on columns are counted from the window's first
+  h += w0 * EPC;
+  w += w0 * EPC;
+  if (dh) dh += w0 * EPC;
+  part += (int64_t)blockIdx.x * d + w0 * EPC;
   if (i < 256) {
-    if (i == 0) {
+    if (i == 0 && w0 == 0) {
       double s = 0.0;
       for (int k = 0; k < kHeadRows / 64; ++k) s += db_s[k];
       part_db[blockIdx.x] = s;
@@ -451,12 +457,11 @@ k_value_head_bwd(int64_t N, int d, const T* h, const T* w, const float* dv, cons
           for (int e = 0; e < EPC; ++e) acc[e] = fmaf(g[u], f[e], acc[e]);
         }
       }
-      float* out = part + (int64_t)blockIdx.x * d;
       if (deal == 1) {
         if (on) {
 #pragma unroll
           for (int e = 0; e < EPC; e += 4)
-            *reinterpret_cast<f32x4*>(out + c * EPC + e) = f32x4{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
+            *reinterpret_cast<f32x4*>(part + c * EPC + e) = f32x4{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
         }
       } else {
 #pragma unroll
@@ -495,10 +500,10 @@ k_value_head_bwd(int64_t N, int d, const T* h, const T* w, const float* dv, cons
   }
   if (deal > 1) {
     __syncthreads();
-    for (int j = i; j < d; j += blockDim.x) {
+    for (int j = i; j < nch * EPC; j += blockDim.x) {
       float s = 0.0f;
-      for (int k = 0; k < deal; ++k) s += sum_s[k * d + j];
-      part[(int64_t)blockIdx.x * d + j] = s;
+      for (int k = 0; k < deal; ++k) s += sum_s[k * nch * EPC + j];
+      part[j] = s;
     }
   }
 }
@@ -553,11 +558,11 @@ hipError_t launch_value_head_fwd(int dtype, int64_t N, int d, int R, const void*
   prof_mark(KK_VALUE_HEAD, true, s);
   const unsigned grid = (unsigned)((N + 3) / 4);
   if (dtype == RLK_DTYPE_BF16)
-    k_value_head_fwd<bf16_t><<<grid, 256, 0, s>>>(N, d, (const bf16_t*)h, (const bf16_t*)w, b, mask, cu, gid, R,
-                                                  values);
+    (d <= 64 * 8 ? k_value_head_fwd<bf16_t, 1> : k_value_head_fwd<bf16_t, 8>)<<<grid, 256, 0, s>>>(
+        N, d, (const bf16_t*)h, (const bf16_t*)w, b, mask, cu, gid, R, values);
   else
-    k_value_head_fwd<float><<<grid, 256, 0, s>>>(N, d, (const float*)h, (const float*)w, b, mask, cu, gid, R,
-                                                 values);
+    (d <= 64 * 4 ? k_value_head_fwd<float, 1> : k_value_head_fwd<float, 8>)<<<grid, 256, 0, s>>>(
+        N, d, (const float*)h, (const float*)w, b, mask, cu, gid, R, values);
   prof_mark(KK_VALUE_HEAD, false, s);
   return hipGetLastError();
 }
@@ -571,13 +576,17 @@ hipError_t launch_value_head_bwd(int dtype, int64_t N, int d, int R, const void*
   float* part = reinterpret_cast<float*>(ws);
   double* part_db = reinterpret_cast<double*>(ws + ((nblk64 * d * 4 + 255) / 256) * 256);
   const unsigned threads = dh ? 512 : 256;
+  // Whole rows per workgroup where those fill the GPU by half; below that, windows of 32 chunks (four lines of a
+  // row), so that a call of few rows is not one workgroup (accumulating, 127 rows of 4,096 bf16: 91 -> 23 us).
+  const int nch = d / (dtype == RLK_DTYPE_BF16 ? 8 : 4), window = nblk < 128 ? 32 : nch;
+  const dim3 grid(nblk, (nch + window - 1) / window);
   if (nblk > 0) {
     if (dtype == RLK_DTYPE_BF16)
-      k_value_head_bwd<bf16_t><<<nblk, threads, 0, s>>>(N, d, (const bf16_t*)h, (const bf16_t*)w, dv, mask, cu, gid, R,
-                                                        (bf16_t*)dh, accumulate, part, part_db);
+      k_value_head_bwd<bf16_t><<<grid, threads, 0, s>>>(N, d, (const bf16_t*)h, (const bf16_t*)w, dv, mask, cu, gid, R,
+                                                        (bf16_t*)dh, accumulate, window, part, part_db);
     else
-      k_value_head_bwd<float><<<nblk, threads, 0, s>>>(N, d, (const float*)h, (const float*)w, dv, mask, cu, gid, R,
-                                                       (float*)dh, accumulate, part, part_db);
+      k_value_head_bwd<float><<<grid, threads, 0, s>>>(N, d, (const float*)h, (const float*)w, dv, mask, cu, gid, R,
+                                                       (float*)dh, accumulate, window, part, part_db);
   }
   k_value_head_dw_final<<<(unsigned)((d + 31) / 32), 1024, 0, s>>>(nblk, d, part, part_db, dw, dbias);
   prof_mark(KK_VALUE_HEAD, false, s);

@@ -226,9 +226,11 @@ def test_gae_and_value_loss_of_many_rollouts(R, mean, off):
 
 
 # rows of fewer than 256 16-byte chunks are dealt among the threads (8 features: 256 rows side by side; 1,360:
-# one row and a rest of idle threads), wider ones take several passes; 128 rows per workgroup
+# one row and a rest of idle threads), wider ones take several passes; 128 rows per workgroup, of fewer than 16,257
+# rows in windows of 32 chunks
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("lens,d", [((1,), 8), ((100, 27), 64), ((128,), 680), ((33, 0, 96), 1360), ((500, 13), 2048), ((61, 70), 4104)])
+@pytest.mark.parametrize("lens,d", [((1,), 8), ((100, 27), 64), ((128,), 680), ((33, 0, 96), 1360), ((500, 13), 2048), ((61, 70), 4104),
+                                    ((16000, 300), 64), ((16256,), 264), ((16257,), 264), ((16400,), 2072)])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_value_head_row_and_column_splits(dtype, lens, d, accumulate):
     ensure_library()
@@ -253,7 +255,7 @@ def test_value_head_row_and_column_splits(dtype, lens, d, accumulate):
     eps = 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -23
     np.testing.assert_allclose(to_host(values)[:, None], (H @ Wv[:, None] + 0.25) * on, rtol=0, atol=2.0 ** -24 * d ** 0.5 * 8 * 4)
     np.testing.assert_allclose(to_host(dh), want, rtol=eps, atol=eps * 1e-2)
-    np.testing.assert_allclose(to_host(dw), (G * H).sum(0), rtol=0, atol=2.0 ** -24 * 128 * 8)
+    np.testing.assert_allclose(to_host(dw), (G * H).sum(0), rtol=2.0 ** -23, atol=2.0 ** -24 * 128 * 8 * max(1.0, N / 128) ** 0.5)
     assert abs(float(db.item()) - G.sum()) <= 2.0 ** -23 * max(1.0, abs(G.sum()))
     assert torch.equal(dw, dw1) and torch.equal(db, db1)
     if accumulate:
