@@ -303,8 +303,8 @@ rlk_status_t layout(const rlk_batch_t* b, bool bwd, int64_t chunk_rows, int64_t 
     L.zr = a.take((size_t)Mc * 4);
     L.st = a.take((size_t)Mc * 4);
     // split-K partials of the dhidden and dW GEMMs (used one after the other)
-    L.sk_dh = splitk_plan(Mc, d, L.Vp * esz);
-    L.sk_dw = splitk_plan(V, d, Mc * esz);
+    L.sk_dh = splitk_plan(Mc, d, L.Vp * esz, esz == 4);
+    L.sk_dw = splitk_plan(V, d, Mc * esz, esz == 4);
     plan_dw_tail(V, d, Mc * esz, L);
     size_t pb = std::max({splitk_bytes(Mc, d, L.sk_dh), splitk_bytes(V, d, L.sk_dw),
                           splitk_bytes(V - L.dw_m0, d, L.sk_dwt)});

@@ -101,7 +101,7 @@ def _bounded_call_is_the_same(dtype, tokens, d, V, outputs):
         assert int(torch.count_nonzero(free[k])) > 0
 
 
-# dhidden of 16 and of 8 output tiles has one split plan: 32 parts of 4 K slices
+# dhidden of 16 and of 8 output tiles has one split plan: 16 parts of 8 K slices
 def test_fp32_dhidden_of_shapes_that_share_a_split_plan():
     _bounded_call_is_the_same("f32", 4096, 256, 4096, ("logp", "ent", "dh"))
 
@@ -119,8 +119,8 @@ def test_fp32_tile_width_does_not_follow_the_bound(tokens, d, V, outputs):
     _bounded_call_is_the_same("f32", tokens, d, V, outputs)
 
 
-# 32 output tiles (128 of 64 columns), 188 K slices in 16 parts: fp32 sums of 384 products.  The gradients are
-# 0.7e-6 off in all, 1.1e-6 and more if a sum runs over the whole vocabulary
+# 32 output tiles (128 of 64 columns), 188 K slices in 8 parts: two fp32 sums of 384 products each.  The gradients
+# are 0.6e-6 off in all, 1.1e-6 and more if a sum runs over the whole vocabulary
 def test_fp32_gradient_sums_stay_short():
     ensure_library()
     cfg, st = _all_policy("f32", 4096, 512, 6000)

@@ -454,7 +454,7 @@ def test_pg_loss_parity_ragged_shapes(name, kw, ent):
 
 
 # Split K: with d = 256 and V = 4096 the dhidden and dW GEMMs have 1 and 16 output tiles a chunk, so both split
-# K (128 slices in 32 parts, 8 in two) and reduce fp32 partials.  Several chunks exercise the dW accumulation across
+# K (128 slices in 16 parts, 8 in two) and reduce fp32 partials.  Several chunks exercise the dW accumulation across
 # chunks.  accumulate_dW adds the gradient to a preset dW (expected: preset + oracle gradient).
 def test_split_k_accumulates_into_preset_dw():
     import torch
