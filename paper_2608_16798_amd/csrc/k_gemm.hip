@@ -724,7 +724,6 @@ __global__ void __launch_bounds__(NT) k_gemm(GemmArgs a) {
 // one barrier per slice and copies one slice ahead hide the memory.  1,024 tokens, d = 256, V = 4,096, against
 // 256 x 256 tiles: forward 75 -> 29 us (64 -> 256 tiles), dhidden 43 -> 27 us, dW 43 -> 26 us.
 constexpr int F_MB = kTile / 4 / 32, F_NB = 2;  // 32x32 MFMA blocks of a wavefront
-using f32x16 = float __attribute__((ext_vector_type(16)));
 
 template <int EPI, bool STORE_Q>
 __global__ void __launch_bounds__(256, 2) k_gemm_f32(GemmArgs a) {

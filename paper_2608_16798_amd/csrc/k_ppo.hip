@@ -388,9 +388,10 @@ k_value_head_fwd(int64_t N, int d, const T* h, const T* w, float b, const uint8_
 // part[blk][j] = sum_t dV_t h_t[j] over its rows (fp32, row order; the thread owns a 16-byte column
 // chunk, and for a row of fewer than 256 chunks the threads deal the rows among themselves and add up
 // in LDS); part_db[blk] = sum_t dV_t (fp64).  131,072 rows of 4,096 bf16, 40 % kept: three passes
-// (dhidden, partial sums of 256 rows four at a time, totals) 615 us -> 320 us with the totals, 4.7 TB/s.  The other 256 (with dh) write the dhidden rows: kept rows
-// get (dh +) dV_t w, the others are zeroed unless accumulating.  Apart, a read's wait does not include
-// the writes issued before it.
+// (dhidden, partial sums of 256 rows four at a time, totals) 615 us -> 320 us with the totals, 4.7 TB/s.
+//   The other 256 (with dh) write the dhidden rows: kept rows get (dh +) dV_t w, the others are zeroed unless
+// accumulating.  Apart, a read's wait does not include the writes issued before it.
+//   A workgroup takes `window` 16-byte chunks of every row (blockIdx.y: which ones).
 template <typename T>
 __global__ void __launch_bounds__(512)
 k_value_head_bwd(int64_t N, int d, const T* h, const T* w, const float* dv, const uint8_t* mask, const int32_t* cu,

@@ -181,7 +181,7 @@ __device__ inline int wave_sum_of(const int32_t* a, int n, int lane) {
 // or, for a rollout of zero advantage, [n_grad, n_eff); its start is the number of earlier tokens of
 // that part, from the block counts and the keep flags of one block).
 //   blkoff: the scanned counts; NULL when the blocks add the counts up themselves (nblk at most
-// kOwnScanBlocks, so four loads per lane and part), which saves the launch of k_scan.  Launch bound: at
+// kOwnScanBlocks, so sixteen loads per lane and part), which saves the launch of k_scan.  Launch bound: at
 // 2,048 tokens count, scan, write and offsets (16 tokens per thread) took 9.8 + 4.4 + 14.4 + 5.1 us, the
 // two launches now 4.6 + 6.0 us.
 constexpr int kOwnScanBlocks = 1024;
@@ -291,8 +291,8 @@ k_write_idx(const uint8_t* keep, const int32_t* cu, int R, int64_t N, const int3
 //   Up to kSortRun rollouts everything is one workgroup and one launch, which also resets the header: an
 // entry per thread, sorted by shuffles (strides below 64) and LDS.  Beyond, one workgroup per run of
 // kSortRun entries sorts it, every entry finds its rank in the other runs by binary search, one workgroup
-// per run counts the group starts before it, and the groups' wavefronts spread over the GPU.  16,384 rollouts: 268 us with one
-// workgroup sorting them all by a bitonic network in LDS, 32 us now (10 + 8 + 9 + 4).
+// per run counts the group starts before it, and the groups' wavefronts spread over the GPU.  16,384 rollouts:
+// 268 us with one workgroup sorting them all by a bitonic network in LDS, 32 us now (10 + 8 + 9 + 4).
 
 constexpr int kSortRun = 1024;
 static_assert(kMaxRollouts % kSortRun == 0, "whole runs");
@@ -585,12 +585,12 @@ hipError_t launch_compact(const uint8_t* mask, const int32_t* cu, const int32_t*
 }
 
 hipError_t launch_begin_advantage(int R, const float* rewards, const int32_t* gid, float adv_eps, int32_t* members,
-                                  int32_t* gstart, int32_t* gidx, int32_t* gsize, double* sort_a, double* sort_b,
+                                  int32_t* gstart, int32_t* gidx, int32_t* gsize, uint64_t* sort_a, uint64_t* sort_b,
                                   float* adv, int32_t* n_groups_out, WsHeader* hdr, const int32_t* cu, int64_t N,
                                   hipStream_t s) {
   if (R > kMaxRollouts) return hipErrorInvalidValue;
   prof_mark(KK_GROUP_RANK, true, s);
-  uint64_t *runs = reinterpret_cast<uint64_t*>(sort_a), *sorted = reinterpret_cast<uint64_t*>(sort_b);
+  uint64_t *runs = sort_a, *sorted = sort_b;
   if (R <= kSortRun) {
     k_advantage_one<<<1, kSortRun, 0, s>>>(rewards, gid, R, adv_eps, members, gstart, gidx, gsize, adv, n_groups_out,
                                            hdr, cu, N);

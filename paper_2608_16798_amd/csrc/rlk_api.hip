@@ -446,8 +446,8 @@ rlk_status_t advantage_call(int32_t R, const float* rewards, const int32_t* grou
   int32_t* gstart = reinterpret_cast<int32_t*>(w + a.take((size_t)(R + 1) * 4));
   int32_t* gidx_ws = reinterpret_cast<int32_t*>(w + a.take((size_t)R * 4));
   int32_t* gsize = reinterpret_cast<int32_t*>(w + a.take((size_t)R * 4));
-  double* sort_a = reinterpret_cast<double*>(w + a.take((size_t)R * 8));
-  double* sort_b = reinterpret_cast<double*>(w + a.take((size_t)R * 8));
+  uint64_t* sort_a = reinterpret_cast<uint64_t*>(w + a.take((size_t)R * 8));
+  uint64_t* sort_b = reinterpret_cast<uint64_t*>(w + a.take((size_t)R * 8));
   int32_t* gidx = group_index ? group_index : gidx_ws;
   RLK_TRY(launch_begin_advantage(R, rewards, group_ids, adv_eps, members, gstart, gidx, gsize, sort_a, sort_b, adv,
                                  n_groups, hdr, nullptr, 0, s),
@@ -692,7 +692,7 @@ rlk_status_t rlk_pg_loss_fwd_bwd(const rlk_batch_t* b, const void* hidden, const
   auto I = [&](size_t off) { return reinterpret_cast<int32_t*>(w + off); };
 
   RLK_TRY(launch_begin_advantage(R, rewards, group_ids, p->adv_eps, I(L.members), I(L.gstart), I(L.gidx), I(L.gsize),
-                                 reinterpret_cast<double*>(w + L.sort_a), reinterpret_cast<double*>(w + L.sort_b),
+                                 reinterpret_cast<uint64_t*>(w + L.sort_a), reinterpret_cast<uint64_t*>(w + L.sort_b),
                                  F(L.adv), nullptr, hdr, b->cu_seqlens, N, s),
           "advantage");
   // With the advantage-weighted surrogate as the only term (no entropy bonus, KL term or per-token

@@ -44,9 +44,9 @@ constexpr float kRefSMin = 1e-30f;
 // s x (rows rounded to 256) x (n rounded to 256) and a reduction kernel adds them in split order.
 // The fp32 tiles of 64 columns, four times as many and two to a compute unit, take two parts of this plan as
 // one: they sum the halves of every slice apart, so their sums are no longer than those of the plan, and the
-// row counts that share a plan (whose dhidden is then bitwise the same) still do.  Half the partials, and still
-// 256 workgroups or more: the debugging batch (1,024 rows, d = 256, V = 4,096) 168 us with the plan as it is, 154 us
-// so; 4,096 rows, d = 512, V = 6,000 455 and 431 us.
+// row counts that share a plan (whose dhidden is then bitwise the same) still do.  Half the partials, and where
+// K is long enough still 256 workgroups or more: the debugging batch (1,024 rows, d = 256, V = 4,096) 168 us
+// with the plan as it is, 154 us so; 4,096 rows, d = 512, V = 6,000 455 and 431 us.
 struct SplitK {
   int s;        // splits (1 = none)
   int kslices;  // K slices per split
@@ -75,14 +75,15 @@ constexpr int kScanTile = 1024;  // tokens per compaction block
 constexpr int kMaxRollouts = 16384;
 constexpr int kRollSums = 8;     // per-rollout fp64 sums of the loss reduction
 
+// The kinds' numbers are part of the interface: those that no launch marks any more keep their place.
 enum KernelKind {
   KK_BEGIN = 0,
   KK_COUNT,
   KK_SCAN,
   KK_WRITE_IDX,
-  KK_ROLLOUT_OFFSETS,
+  KK_ROLLOUT_OFFSETS,  // not marked: in KK_WRITE_IDX
   KK_GROUP_RANK,
-  KK_GROUP_STATS,
+  KK_GROUP_STATS,      // not marked: in KK_GROUP_RANK or KK_ADVANTAGE
   KK_ADVANTAGE,
   KK_TRANSPOSE_W,
   KK_GATHER,
@@ -124,7 +125,7 @@ struct WsLayout {
   size_t blkcnt = 0, blkoff = 0;
   // rollouts [R]
   size_t rstart = 0, rnpol = 0, members = 0, gstart = 0, gidx = 0, gsize = 0, adv = 0;
-  size_t sort_a = 0, sort_b = 0;   // uint64 [R]: sort scratch of the advantages
+  size_t sort_a = 0, sort_b = 0;   // uint64_t [R]: sort scratch of the advantages
   size_t rsum = 0;  // double [R][kRollSums]
   // chunk buffers
   size_t pm = 0, ps = 0, pu = 0;   // float [nvt][Mc]
@@ -168,7 +169,7 @@ hipError_t launch_compact(const uint8_t* mask, const int32_t* cu, const int32_t*
 // groups, group by group), gstart [R + 1] (run starts), gidx [R], gsize (per group), adv [R];
 // n_groups_out may be NULL; sort_a, sort_b: 8 bytes of scratch per rollout each.  R <= kMaxRollouts.
 hipError_t launch_begin_advantage(int R, const float* rewards, const int32_t* gid, float adv_eps, int32_t* members,
-                                  int32_t* gstart, int32_t* gidx, int32_t* gsize, double* sort_a, double* sort_b,
+                                  int32_t* gstart, int32_t* gidx, int32_t* gsize, uint64_t* sort_a, uint64_t* sort_b,
                                   float* adv, int32_t* n_groups_out, WsHeader* hdr, const int32_t* cu, int64_t N,
                                   hipStream_t s);
 
