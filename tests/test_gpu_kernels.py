@@ -87,7 +87,8 @@ def test_fp32_gemm_tile_edges(tokens, d, V, entropy):
 
 
 def _bounded_call_is_the_same(dtype, tokens, d, V, outputs):
-    """Every second token trained: a call bounded by their number (half the chunk rows) against one without."""
+    """Every second token trained: a call bounded by their number (half the chunk rows) against one without, and
+    the per-token outputs of one in chunks of 1,024 rows."""
     ensure_library()
     cfg, st = _all_policy(dtype, tokens, d, V)
     mask = np.ones_like(st.mask)
@@ -99,6 +100,11 @@ def _bounded_call_is_the_same(dtype, tokens, d, V, outputs):
     for k in outputs:
         assert torch.equal(free[k], bounded[k]), k
         assert int(torch.count_nonzero(free[k])) > 0
+    chunked = run_gpu(inst, params_for(cfg, chunk_rows=1024))
+    assert chunked["stats"]["n_chunks"] > free["stats"]["n_chunks"]
+    for k in ("logp", "ent"):
+        assert torch.equal(free[k], chunked[k]), k
+    assert free["loss"] == bounded["loss"] == chunked["loss"]
 
 
 # dhidden of 16 and of 8 output tiles has one split plan: 16 parts of 8 K slices
