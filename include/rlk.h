@@ -258,7 +258,7 @@ rlk_status_t rlk_gae(int64_t N, int32_t R, const int32_t* cu_seqlens, const uint
  * rollouts of (values[t] - returns[t])^2 (0 when there is none); dvalues[t] = dloss/dvalues[t]
  * = 2 (values[t] - returns[t]) / count on those rows, 0 elsewhere (dvalues may be NULL).
  * Device pointers as in rlk_gae; loss device float[1].  ws: rlk_value_workspace_size bytes,
- * 256-byte aligned, deterministic reduction (per-rollout fp64 partial sums). */
+ * 256-byte aligned, deterministic reduction (fp64 partial sums of slices of the rollouts). */
 rlk_status_t rlk_value_workspace_size(int32_t R, size_t* bytes);
 rlk_status_t rlk_value_loss(int64_t N, int32_t R, const int32_t* cu_seqlens, const uint8_t* mask,
                             const float* values, const float* returns, const int32_t* group_ids, float* loss,
@@ -277,7 +277,7 @@ rlk_status_t rlk_value_head_fwd(const rlk_batch_t* b, const void* hidden, const 
  * computes, dhidden[t] = dvalues[t] w_v, added to dhidden when accumulate = 1 (other rows then
  * untouched) and written otherwise (other rows then set to 0); dhidden may be NULL (skipped).
  * dw_v [d] f32 = sum_t dvalues[t] hidden[t] and db_v [1] f32 = sum_t dvalues[t] over those rows,
- * from per-256-row partial sums added in row order (deterministic).  ws:
+ * from partial sums of 128 rows each, added in a fixed order (deterministic).  ws:
  * rlk_value_head_workspace_size bytes, 256-byte aligned. */
 rlk_status_t rlk_value_head_workspace_size(const rlk_batch_t* b, size_t* bytes);
 rlk_status_t rlk_value_head_bwd(const rlk_batch_t* b, const void* hidden, const void* w_v, const uint8_t* mask,

@@ -112,6 +112,16 @@ def test_fp32_dhidden_of_shapes_that_share_a_split_plan():
     _bounded_call_is_the_same("f32", 4096, 256, 4096, ("logp", "ent", "dh"))
 
 
+# dhidden of 40 x 9 tiles from W itself, the tile rows of the partial last wave split over K in a second launch; the
+# last K slice holds 17 rows of W
+def test_k_major_dhidden_with_a_split_tail():
+    ensure_library()
+    cfg, st = _all_policy("bf16", 10000, 2056, 2001)
+    inst = build_instance(cfg, structure=st)
+    p = params_for(cfg)
+    compare_full(inst, run_gpu(inst, p, max_policy_tokens=10000), run_oracle(inst, p), p, tag="K-major tail")
+
+
 # bf16: W^T without the bound, W itself (K-major) with it: the same products in the same order
 def test_bf16_dhidden_from_w_and_from_its_transpose_are_the_same():
     _bounded_call_is_the_same("bf16", 32768, 136, 250, ("logp", "ent", "dh"))
