@@ -578,22 +578,46 @@ def value_head_bwd(hidden, w_v, mask, cu_seqlens, group_ids, dvalues, dhidden=No
     return dhidden, dw_v, db_v
 
 
-def _token_array(tokens):
-    """A call's tokens as int32.  Integer arrays and lists of plain ints are converted as a whole (0.5 million
-    tokens, the whole packing: arrays 58.7 -> 0.42 ms; lists on a slower host 112 -> 31 ms); anything else token by token, as int() takes it."""
+def _int32_tokens(a):
     import numpy as np
 
-    a = tokens
-    if isinstance(a, (list, tuple)) and len(a) and type(a[0]) is int:
-        try:
-            a = np.array(a)
-        except (ValueError, TypeError, RuntimeError):
-            pass
-    if not (isinstance(a, np.ndarray) and a.ndim == 1 and a.dtype.kind in "iu"):
-        return np.asarray([int(t) for t in tokens], np.int32)
     if a.dtype != np.int32 and a.size and (a.min() < -2 ** 31 or a.max() >= 2 ** 31):
         raise OverflowError("token out of bounds for int32")
     return a.astype(np.int32, copy=False)
+
+
+def _flat_tokens(sequences):
+    """Token sequences one after the other as int32, and their offsets.  Integer arrays are joined and lists of
+    plain ints converted as a whole, many short ones together (0.5 million tokens, the whole packing: arrays
+    58.7 -> 0.42 ms; lists on a slower host 112 -> 31 ms); anything else token by token, as int() takes it."""
+    import numpy as np
+
+    parts, run, off = [], [], [0]
+
+    def end_run():
+        if run:
+            try:
+                a = np.array(run)
+            except (ValueError, TypeError, RuntimeError, OverflowError):
+                a = None
+            if a is None or a.ndim != 1 or a.dtype.kind not in "iu":
+                a = np.asarray([int(t) for t in run], np.int32)
+            parts.append(_int32_tokens(a))
+            run.clear()
+
+    for s in sequences:
+        if isinstance(s, np.ndarray) and s.ndim == 1 and s.dtype.kind in "iu":
+            end_run()
+            # a uint64 beside signed integers would join as floating point
+            parts.append(_int32_tokens(s) if s.dtype.kind == "u" else s)
+            off.append(off[-1] + s.size)
+        else:
+            n = len(run)
+            run.extend(s if isinstance(s, (list, tuple)) else [int(t) for t in s])
+            off.append(off[-1] + len(run) - n)
+    end_run()
+    flat = _int32_tokens(np.concatenate(parts)) if parts else np.empty(0, np.int32)
+    return flat, np.asarray(off, np.int64)
 
 
 def _calls_struct(calls_per_rollout):
@@ -603,12 +627,11 @@ def _calls_struct(calls_per_rollout):
     call_off, xs, ys = [0], [], []
     for calls in calls_per_rollout:
         for x, y in calls:
-            xs.append(_token_array(x))
-            ys.append(_token_array(y))
+            xs.append(x)
+            ys.append(y)
         call_off.append(len(xs))
-    off = lambda parts: np.cumsum([0] + [p.size for p in parts], dtype=np.int64)
-    flat = lambda parts: np.concatenate(parts) if parts else np.empty(0, np.int32)
-    arrs = dict(call_off=np.asarray(call_off, np.int64), x_off=off(xs), y_off=off(ys), x_tok=flat(xs), y_tok=flat(ys))
+    (x_tok, x_off), (y_tok, y_off) = _flat_tokens(xs), _flat_tokens(ys)
+    arrs = dict(call_off=np.asarray(call_off, np.int64), x_off=x_off, y_off=y_off, x_tok=x_tok, y_tok=y_tok)
     c = Calls(R=len(calls_per_rollout), **{k: v.ctypes.data for k, v in arrs.items()})
     return c, arrs
 

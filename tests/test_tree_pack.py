@@ -159,3 +159,29 @@ def test_library_tree_pack_refuses_tokens_past_int32(bad):
 
     with pytest.raises(OverflowError):
         rlk.tree_pack([[(bad, [1])]])
+
+
+def test_library_tree_pack_takes_different_sequences_in_one_batch():
+    """Neighbouring lists are converted together: every form beside every other one, in contexts and responses."""
+    import paper_2608_16798_amd as rlk
+
+    forms = [list, lambda t: np.asarray(t, np.int32), tuple, lambda t: np.asarray(t, np.uint64), list, list,
+             lambda t: np.asarray(t, np.int64), lambda t: [float(v) for v in t], list, lambda t: [str(v) for v in t],
+             lambda t: np.asarray(t, ">i4"), lambda t: iter(t), lambda t: [np.uint64(v) for v in t], list,
+             lambda t: np.asarray(t, np.float64), lambda t: np.asarray(t, np.int8)]
+    rng = np.random.default_rng(10)
+    rolls = [random_calls(rng, n_calls=9) for _ in range(9)] + [[], [([], [])]]
+    want = O.tree_pack(rolls)
+    n = 0
+    mixed = []
+    for calls in rolls:
+        mixed.append([])
+        for x, y in calls:
+            mixed[-1].append((forms[n % len(forms)](x), forms[(n + n // len(forms)) % len(forms)](y)))
+            n += 1
+    got = rlk.tree_pack(mixed)
+    for k in want:
+        np.testing.assert_array_equal(np.asarray(got[k]), want[k], err_msg=k)
+    for bad in ([2 ** 31], [-1, 2 ** 63], np.asarray([2 ** 63], np.uint64), [1.0, 2.0 ** 31]):
+        with pytest.raises(OverflowError):
+            rlk.tree_pack([[([1, 2], [3]), (bad, [1]), ([1, 2, 3], [4])]])
