@@ -222,7 +222,7 @@ __global__ void __launch_bounds__(256) k_hidden_t(const uint16_t* hc, int d, con
 // do not depend on the chunk rows.
 // Bound by the latency of the loads: few tokens are dealt in blocks of 16, with 64 strides of tiles side by
 // side, many in blocks of 64, whose loads are whole lines.  Against blocks of 64 tokens on four wavefronts, one
-// tile in flight: 160 tokens of 594 tiles 107 -> 9 us, 770 tokens 127 -> 14 us, 23,000 tokens of 196 tiles 52 -> 20 us.
+// tile in flight: 160 tokens of 594 tiles 107 -> 9 us, 770 tokens 127 -> 14 us, 23,000 tokens of 196 tiles 52 -> 22 us.
 constexpr int kCombineWaves = 16;
 
 // (M, S, T) += (m, s, t), both relative to their own maximum (-inf: no tile, sums of 0, or of NaN where all
